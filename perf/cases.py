@@ -21,6 +21,7 @@ tokens does not hang on the last bit of a logit.
 from __future__ import annotations
 
 import math
+import weakref
 
 import torch
 
@@ -184,9 +185,7 @@ class _Handle:
 
     def __init__(self, f):
         self.f = f
-
-    def __del__(self):
-        F.fleet_destroy(self.f)
+        weakref.finalize(self, F.fleet_destroy, f)
 
 
 def run(s):
