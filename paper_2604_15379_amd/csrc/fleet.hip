@@ -30,7 +30,9 @@ FLEET_EXTERN_VARIANT(4) FLEET_EXTERN_VARIANT(5) FLEET_EXTERN_VARIANT(6)
 // activations, partial sums, counters and status block of one step live in this array
 // instead of the fleet's own allocation.  Host code never uses the array's name as an
 // address: the device address is looked up once per device (static_workspace()).
-static __device__ __align__(256) unsigned char fleet_static_scratch[FLEET_STATIC_SCRATCH_BYTES];
+// (4 KB more than the bytes a step may need: the counter block's head has one cache line per
+// word that many workers touch, which the limit does not count)
+static __device__ __align__(256) unsigned char fleet_static_scratch[FLEET_STATIC_SCRATCH_BYTES + 4096];
 
 namespace {
 
@@ -287,6 +289,13 @@ size_t work_layout(const fleet* f, const DevGraph* dg, char* base, Work* w) {
   return off;
 }
 
+// What a step of graph dg counts against FLEET_STATIC_SCRATCH_BYTES: its working memory with the
+// counter block's head at 96 words.
+size_t static_need(const fleet* f, const DevGraph* dg) {
+  const size_t words = (size_t)dg->ctr_words;
+  return work_layout(f, dg, nullptr, nullptr) - align_up(words * 4) + align_up((words - dev::C_EVENTS + 96) * 4);
+}
+
 int resolve_weight(const fleet* f, int wkind, int layer, const void* const* gemm_copies, bool packed,
                    const void** first, const void** second) {
   *first = *second = nullptr;
@@ -388,9 +397,10 @@ int launch(dev::Params& P, DevGraph* dg, int n_cu, int preset_event, hipStream_t
   return launch_persistent(dg, P, n_cu, st);
 }
 
-void fill_graph_params(dev::Params& P, const DevGraph* dg) {
+void fill_graph_params(dev::Params& P, const DevGraph* dg, const DevInfo& info) {
   P.ops = dg->ops; P.tasks = dg->tasks; P.events = dg->events; P.qoff = dg->qoff; P.qents = dg->qents;
   P.fat = dg->fat; P.n_events = dg->g.n_events(); P.gcnt_base = dg->gcnt_base;
+  for (int x = 0; x < dev::MAX_XCD; ++x) P.n_expect[x] = info.per_xcd[x];
 }
 
 // the graph that serves a step of `batch` sequences: the smallest bucket that holds it
@@ -431,7 +441,7 @@ int run_layers(fleet* f, const StepArgs& a, hipStream_t st) {
   const Graph& g = dg->g;
   Work w;
   if (a.static_ws) {
-    if (work_layout(f, dg, nullptr, nullptr) > (size_t)FLEET_STATIC_SCRATCH_BYTES) return FLEET_ETOOBIG;
+    if (static_need(f, dg) > (size_t)FLEET_STATIC_SCRATCH_BYTES) return FLEET_ETOOBIG;
     void* base = nullptr;
     int rc = static_workspace(&base);   // looked up by fleet_create on this device: a table read here
     if (rc) return rc;
@@ -442,7 +452,7 @@ int run_layers(fleet* f, const StepArgs& a, hipStream_t st) {
   const int L = f->shape.n_layers, nm = n_marks(L), nx = f->info.n_xcd;
   dev::Params P;
   memset(&P, 0, sizeof(P));
-  fill_graph_params(P, dg);
+  fill_graph_params(P, dg, f->info);
   P.ctr = w.ctr; P.status = w.status;
   P.buf[BUF_X] = w.x; P.buf[BUF_N] = w.n; P.buf[BUF_QKV] = w.qkv; P.buf[BUF_ATT] = w.att; P.buf[BUF_H] = w.h;
   P.buf[BUF_PART] = w.part; P.buf[BUF_GPART] = w.gpart; P.buf[BUF_GU32] = w.gu32; P.buf[BUF_SS] = w.ss;
@@ -495,7 +505,7 @@ int warm_kernels(fleet* f) {
     for (int paged = 0; paged < 2; ++paged) {
       dev::Params P;
       memset(&P, 0, sizeof(P));
-      fill_graph_params(P, dg);
+      fill_graph_params(P, dg, f->info);
       P.n_events = 0;   // no event table to cache, no task to run
       P.ctr = w.ctr; P.status = w.status;
       P.n_iter = 1; P.n_xcd = f->info.n_xcd; P.flags = f->shape.flags & ~(FLEET_FLAG_TRACE | FLEET_FLAG_TIMING);
@@ -810,7 +820,7 @@ int fleet_gemm(int32_t B, int32_t K, int32_t N, const void* x, const void* const
   if ((rc = upload(&gpart, nullptr, gpart_bytes * (sched_mode == FLEET_SCHED_UNAWARE ? 1 : dev::MAX_XCD)))) { free_all(); return rc; }
   dev::Params P;
   memset(&P, 0, sizeof(P));
-  fill_graph_params(P, &dg);
+  fill_graph_params(P, &dg, info);
   P.ctr = ctr;
   P.buf[BUF_GEMM_X] = mfma ? xp : (void*)x; P.buf[BUF_GEMM_Y] = y; P.buf[BUF_GPART] = gpart;
   P.gpart_xcd_bytes = sched_mode == FLEET_SCHED_UNAWARE ? 0 : (int32_t)gpart_bytes;
