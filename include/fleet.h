@@ -169,7 +169,7 @@ int fleet_create(const fleet_shape_t *shape, const fleet_weights_t *weights, fle
  *              layer and the final norm (no LM head)
  * hidden_in, the caches, hidden_out and logits must be 16-byte aligned (FLEET_EINVAL
  * otherwise): the kernels move them in 16-byte pieces.
- * The call launches two kernels on `stream` and does nothing else: no allocation, no
+ * The call launches one kernel on `stream` and does nothing else: no allocation, no
  * copy, no synchronisation (it can be captured into a HIP graph).
  * A dependency wait that times out aborts the step on the device; the next
  * fleet_last_status() reports FLEET_ETIMEOUT.
@@ -206,8 +206,8 @@ int fleet_destroy(fleet_t *f);
  * are bit-identical to it.  A step whose working memory exceeds the array (large batches on
  * the MFMA path with split-K partial sums; the Qwen3-8B shape fits up to batch 16) is
  * refused with FLEET_ETOOBIG before anything is launched.  The call itself allocates
- * nothing, frees nothing and copies nothing from the host; counters and status are cleared
- * by a kernel at the start of every call.  All calls on one GPU share the array: calls
+ * nothing, frees nothing and copies nothing from the host; every launch leaves the counters
+ * cleared for the next one.  All calls on one GPU share the array: calls
  * that overlap on one GPU (two streams, two fleets, two threads) race; calls on one stream
  * are safe.  fleet_last_status reports on the last step launched either way.
  */

@@ -27,12 +27,16 @@ FLEET_EXTERN_VARIANT(4) FLEET_EXTERN_VARIANT(5) FLEET_EXTERN_VARIANT(6)
 #undef FLEET_EXTERN_VARIANT
 
 // Workspace of fleet_decode_step_static, the entry point that allocates nothing: the
-// activations, partial sums, counters and status block of one step live in this array
+// activations, partial sums and counters of one step live in this array
 // instead of the fleet's own allocation.  Host code never uses the array's name as an
 // address: the device address is looked up once per device (static_workspace()).
-// (4 KB more than the bytes a step may need: the counter block's head has one cache line per
-// word that many workers touch, which the limit does not count)
-static __device__ __align__(256) unsigned char fleet_static_scratch[FLEET_STATIC_SCRATCH_BYTES + 4096];
+// In front of it lies the counter block, at the same place and of the same size for every fleet and
+// graph, because a launch leaves a clean set of counters for the next: room for the largest a graph
+// can have.
+constexpr size_t STATIC_SET_WORDS = ((size_t)dev::C_EVENTS + (size_t)dev::ECACHE * (1 + dev::MAX_XCD) + dev::N_PAIR +
+                                     (size_t)dev::COPY_GROUPS * dev::MAX_XCD * dev::ECACHE + dev::GEMM_CNT_WORDS + 31) / 32 * 32;
+constexpr size_t STATIC_CTR_BYTES = ((dev::CTR_HEAD + 2 * STATIC_SET_WORDS) * 4 + 255) / 256 * 256;
+static __device__ __align__(256) unsigned char fleet_static_scratch[STATIC_CTR_BYTES + FLEET_STATIC_SCRATCH_BYTES];
 
 namespace {
 
@@ -48,13 +52,13 @@ struct DevInfo {
 };
 
 // Device memory one launch works in besides the caller's buffers and the graph's
-// descriptors: activations, partial sums, the counter block and the status block, carved
+// descriptors: activations, partial sums and the counter block, carved
 // from one base (the fleet's own allocation, or the static workspace).
 struct Work {
   float* x = nullptr; void* n = nullptr; float* qkv = nullptr; void* att = nullptr; void* h = nullptr;
   float* part = nullptr; float* gpart = nullptr; float* gu32 = nullptr;
   float* ss = nullptr;       // sums of squares of the residual rows, per 16 features
-  uint32_t* ctr = nullptr; int32_t* status = nullptr;
+  uint32_t* ctr_block = nullptr; int ctr_set_words = 0;
   size_t gpart_region = 0;   // bytes between the per-XCD regions of gpart
 };
 
@@ -62,7 +66,7 @@ struct DevGraph {
   Graph g;
   int32_t *ops = nullptr, *tasks = nullptr, *events = nullptr, *qoff = nullptr, *qents = nullptr;
   int32_t* fat = nullptr;   // [n_tasks][FAT_WORDS]: task words, op words, weight pointers, id
-  int ctr_words = 0, gcnt_base = 0;
+  int ctr_words = 0, gcnt_base = 0;   // words of counters (a set), first of the split-K tile counters
   ~DevGraph() {
     for (void* p : {(void*)ops, (void*)tasks, (void*)events, (void*)qoff, (void*)qents, (void*)fat})
       if (p) (void)hipFree(p);
@@ -230,12 +234,14 @@ struct fleet {
   std::vector<int> buckets;
   std::vector<std::unique_ptr<DevGraph>> graphs;        // by bucket
   std::vector<std::unique_ptr<DevGraph>> graphs_loop;   // with the next-token stage (multi-step launches)
-  char* work = nullptr;      // the fleet's own working memory (layout: work_layout())
-  size_t work_bytes = 0;
+  char* work = nullptr;      // the fleet's own working memory: the counter block, then work_layout()
+  int ctr_set_words = 0;
+  size_t ctr_bytes = 0, work_bytes = 0;
   float2* rope = nullptr;
   int32_t* trace = nullptr;
   long long timeout_ticks = 0;
-  int32_t* last_status = nullptr;   // status block of the last launch (device)
+  const uint32_t* last_ctr_block = nullptr;   // counter block of the last launch (device)
+  int last_set_words = 0;
   float* last_x = nullptr;          // residual stream of the last launch (device)
 
   ~fleet() {
@@ -249,8 +255,8 @@ struct fleet {
 
 namespace {
 
-// Working memory of one launch of graph dg, carved from `base` (may be null: sizes only).
-// Returns the bytes needed.
+// Working memory of one launch of graph dg besides the counter block, carved from `base` (may be
+// null: sizes only).  Returns the bytes needed.
 size_t work_layout(const fleet* f, const DevGraph* dg, char* base, Work* w) {
   const Graph& g = dg->g;
   const fleet_shape_t& s = f->shape;
@@ -279,21 +285,43 @@ size_t work_layout(const fleet* f, const DevGraph* dg, char* base, Work* w) {
   char* gpart = take(gp * regions);
   char* gu32 = take((s.flags & FLEET_FLAG_UNFUSED_SILU) ? B * 2 * F * 4 : 0);
   char* ss = take(B * (H / 16) * 4);
-  char* ctr = take((size_t)dg->ctr_words * 4);
-  char* status = take(dev::ST_WORDS * 4);
   if (w) {
     w->x = (float*)x; w->n = n; w->qkv = (float*)qkv; w->att = att; w->h = h; w->part = (float*)part;
-    w->gpart = (float*)gpart; w->gu32 = (float*)gu32; w->ss = (float*)ss; w->ctr = (uint32_t*)ctr; w->status = (int32_t*)status;
+    w->gpart = (float*)gpart; w->gu32 = (float*)gu32; w->ss = (float*)ss;
     w->gpart_region = gp;
   }
   return off;
 }
 
-// What a step of graph dg counts against FLEET_STATIC_SCRATCH_BYTES: its working memory with the
-// counter block's head at 96 words.
+int ctr_set_words(const DevGraph* dg) { return (dg->ctr_words + 31) / 32 * 32; }
+size_t ctr_block_bytes(int set_words) { return align_up((dev::CTR_HEAD + 2 * (size_t)set_words) * 4); }
+// the fleet's own working memory for graph dg: the counter block sits at the same place for all
+// graphs and its sets hold the largest graph's counters (the next launch may run any of them)
+void own_work(const fleet* f, const DevGraph* dg, Work* w) {
+  work_layout(f, dg, f->work + f->ctr_bytes, w);
+  w->ctr_block = (uint32_t*)f->work;
+  w->ctr_set_words = f->ctr_set_words;
+}
+// What a step of graph dg counts against FLEET_STATIC_SCRATCH_BYTES: its working memory, one set of
+// counters with a head of 96 words, and 256 bytes of status.
 size_t static_need(const fleet* f, const DevGraph* dg) {
-  const size_t words = (size_t)dg->ctr_words;
-  return work_layout(f, dg, nullptr, nullptr) - align_up(words * 4) + align_up((words - dev::C_EVENTS + 96) * 4);
+  return work_layout(f, dg, nullptr, nullptr) + align_up(((size_t)dg->ctr_words - dev::C_EVENTS + 96) * 4) + 256;
+}
+// The outcome of the last launch that used the counter block, from its set (the head word already
+// names the other one): the first abort report, and the workers per XCD.
+int read_status(const uint32_t* block, int set_words, fleet_status_t* out) {
+  uint32_t set = 0, w[dev::C_READY];
+  HIP_TRY(hipMemcpy(&set, block, sizeof(set), hipMemcpyDeviceToHost));
+  HIP_TRY(hipMemcpy(w, block + dev::CTR_HEAD + (size_t)((set & 1) ^ 1) * set_words, sizeof(w), hipMemcpyDeviceToHost));
+  const bool aborted = w[dev::C_ABORT] != 0;
+  const uint32_t* rep = w + dev::C_REPORT;
+  out->code = aborted ? (int32_t)rep[0] : FLEET_OK;
+  out->task = aborted ? (int32_t)rep[1] : -1;
+  out->event = aborted ? (int32_t)rep[2] : 0;
+  out->observed = aborted ? (int32_t)rep[3] : 0;
+  out->needed = aborted ? (int32_t)rep[4] : 0;
+  for (int x = 0; x < dev::MAX_XCD; ++x) out->workers[x] = (int32_t)w[dev::C_ROSTER + 32 * x];
+  return FLEET_OK;
 }
 
 int resolve_weight(const fleet* f, int wkind, int layer, const void* const* gemm_copies, bool packed,
@@ -381,25 +409,10 @@ int upload_graph(DevGraph* dg, const fleet* f, const void* const* gemm_copies, i
   return FLEET_OK;
 }
 
-// reset counters and status, then run queue slice [q_begin, q_end) of every XCD
-int launch(dev::Params& P, DevGraph* dg, int n_cu, int preset_event, hipStream_t st) {
-  const int words = dg->ctr_words;
-  int preset_word = -1;
-  uint32_t preset_val = 0;
-  if (preset_event >= 0) {
-    preset_word = dev::C_EVENTS + preset_event;
-    preset_val = 0x40000000u;   // satisfied whatever the threshold
-  }
-  const int nE = dg->g.n_events(), nx = dg->g.header[H_N_XCD], cstride = (nE + 31) & ~31;
-  const int cbase = dev::C_EVENTS + nE * (1 + nx) + dev::N_PAIR;
-  hipLaunchKernelGGL(fleet_reset_kernel, dim3((words + 255) / 256), dim3(256), 0, st, P.ctr, words, preset_word,
-                     preset_val, P.status, cbase, cstride, dev::COPY_GROUPS * nx, preset_event);
-  return launch_persistent(dg, P, n_cu, st);
-}
-
 void fill_graph_params(dev::Params& P, const DevGraph* dg, const DevInfo& info) {
   P.ops = dg->ops; P.tasks = dg->tasks; P.events = dg->events; P.qoff = dg->qoff; P.qents = dg->qents;
   P.fat = dg->fat; P.n_events = dg->g.n_events(); P.gcnt_base = dg->gcnt_base;
+  P.preset_event = -1;
   for (int x = 0; x < dev::MAX_XCD; ++x) P.n_expect[x] = info.per_xcd[x];
 }
 
@@ -445,15 +458,17 @@ int run_layers(fleet* f, const StepArgs& a, hipStream_t st) {
     void* base = nullptr;
     int rc = static_workspace(&base);   // looked up by fleet_create on this device: a table read here
     if (rc) return rc;
-    work_layout(f, dg, (char*)base, &w);
+    work_layout(f, dg, (char*)base + STATIC_CTR_BYTES, &w);
+    w.ctr_block = (uint32_t*)base;
+    w.ctr_set_words = (int)STATIC_SET_WORDS;
   } else {
-    work_layout(f, dg, f->work, &w);
+    own_work(f, dg, &w);
   }
   const int L = f->shape.n_layers, nm = n_marks(L), nx = f->info.n_xcd;
   dev::Params P;
   memset(&P, 0, sizeof(P));
   fill_graph_params(P, dg, f->info);
-  P.ctr = w.ctr; P.status = w.status;
+  P.ctr_block = w.ctr_block; P.ctr_set_words = w.ctr_set_words;
   P.buf[BUF_X] = w.x; P.buf[BUF_N] = w.n; P.buf[BUF_QKV] = w.qkv; P.buf[BUF_ATT] = w.att; P.buf[BUF_H] = w.h;
   P.buf[BUF_PART] = w.part; P.buf[BUF_GPART] = w.gpart; P.buf[BUF_GU32] = w.gu32; P.buf[BUF_SS] = w.ss;
   P.buf[BUF_HIDDEN_IN] = (void*)a.hidden_in; P.buf[BUF_TOKENS] = (void*)a.tokens;
@@ -484,10 +499,11 @@ int run_layers(fleet* f, const StepArgs& a, hipStream_t st) {
     hipLaunchKernelGGL(fleet_row_ss_kernel, dim3(std::max(1, a.batch * (f->shape.hidden / 16) / 256)), dim3(256), 0, st,
                        (const float*)w.x, w.ss, a.batch, f->shape.hidden);
   }
-  const int preset = a.with_ingest ? -1 : g.xready[a.layer_begin];
-  f->last_status = w.status;
+  if (!a.with_ingest) P.preset_event = g.xready[a.layer_begin];
+  f->last_ctr_block = w.ctr_block;
+  f->last_set_words = w.ctr_set_words;
   f->last_x = w.x;
-  return launch(P, dg, f->info.n_cu, preset, st);
+  return launch_persistent(dg, P, f->info.n_cu, st);
 }
 
 // Launch every kernel flavour the fleet's graphs use once, on empty queues (the workers start
@@ -501,17 +517,17 @@ int warm_kernels(fleet* f) {
     if (seen[v]) continue;
     seen[v] = true;
     Work w;
-    work_layout(f, dg, f->work, &w);
+    own_work(f, dg, &w);
     for (int paged = 0; paged < 2; ++paged) {
       dev::Params P;
       memset(&P, 0, sizeof(P));
       fill_graph_params(P, dg, f->info);
       P.n_events = 0;   // no event table to cache, no task to run
-      P.ctr = w.ctr; P.status = w.status;
+      P.ctr_block = w.ctr_block; P.ctr_set_words = w.ctr_set_words;
       P.n_iter = 1; P.n_xcd = f->info.n_xcd; P.flags = f->shape.flags & ~(FLEET_FLAG_TRACE | FLEET_FLAG_TIMING);
       P.timeout_ticks = f->timeout_ticks; P.batch = 1; P.hidden = f->shape.hidden;
       P.page_size = paged ? 64 : 0; P.n_pages = paged;
-      int rc = launch(P, dg, f->info.n_cu, -1, nullptr);
+      int rc = launch_persistent(dg, P, f->info.n_cu, nullptr);
       if (rc) return rc;
     }
   }
@@ -611,15 +627,17 @@ int fleet_create(const fleet_shape_t* shape, const fleet_weights_t* w, fleet_t**
       dg->g = build_decode_graph(f->shape, b, f->info.n_xcd, f->info.n_cu, loop != 0, f->fma_max);
       if ((rc = upload_graph(dg.get(), f.get(), nullptr, f->info.n_xcd))) return rc;
       f->work_bytes = std::max(f->work_bytes, work_layout(f.get(), dg.get(), nullptr, nullptr));
+      f->ctr_set_words = std::max(f->ctr_set_words, ctr_set_words(dg.get()));
       (loop ? f->graphs_loop : f->graphs).push_back(std::move(dg));
     }
-  if ((rc = upload(&f->work, nullptr, f->work_bytes))) return rc;
+  f->ctr_bytes = ctr_block_bytes(f->ctr_set_words);
+  if ((rc = upload(&f->work, nullptr, f->ctr_bytes + f->work_bytes))) return rc;
+  HIP_TRY(hipMemset(f->work, 0, f->ctr_bytes));
   if ((rc = warm_kernels(f.get()))) return rc;
-  {   // a status block that reads "ok" before the first step
+  {   // what fleet_last_status reads before the first step
     Work w0;
-    work_layout(f.get(), f->graphs[0].get(), f->work, &w0);
-    HIP_TRY(hipMemset(w0.status, 0, dev::ST_WORDS * 4));
-    f->last_status = w0.status; f->last_x = w0.x;
+    own_work(f.get(), f->graphs[0].get(), &w0);
+    f->last_ctr_block = w0.ctr_block; f->last_set_words = w0.ctr_set_words; f->last_x = w0.x;
   }
   if (shape->flags & (FLEET_FLAG_TRACE | FLEET_FLAG_TIMING))
     if ((rc = upload(&f->trace, nullptr, ((size_t)f->info.n_cu * TRACE_CAP * 8 + f->info.n_cu) * 4))) return rc;
@@ -724,13 +742,10 @@ int fleet_last_status(fleet_t* f, fleet_status_t* out) {
   memset(out, 0, sizeof(*out));
   hipError_t e = hipDeviceSynchronize();
   out->hip_error = e != hipSuccess ? (int)e : g_last_hip;
-  int32_t st[dev::ST_WORDS];
-  HIP_TRY(hipMemcpy(st, f->last_status, sizeof(st), hipMemcpyDeviceToHost));
-  out->code = e != hipSuccess ? FLEET_EHIP : st[dev::ST_CODE];
-  out->task = st[dev::ST_TASK]; out->event = st[dev::ST_EVENT];
-  out->observed = st[dev::ST_OBSERVED]; out->needed = st[dev::ST_NEEDED];
+  int rc = read_status(f->last_ctr_block, f->last_set_words, out);
+  if (rc) return rc;
+  if (e != hipSuccess) out->code = FLEET_EHIP;
   out->n_xcd = f->info.n_xcd;
-  for (int x = 0; x < 8; ++x) out->workers[x] = st[dev::ST_WORKERS + x];
   return FLEET_OK;
 }
 
@@ -797,12 +812,11 @@ int fleet_gemm(int32_t B, int32_t K, int32_t N, const void* x, const void* const
   const bool mfma = dg.g.header[H_PATH] == P_MFMA;
   std::vector<void*> packed;
   void* xp = nullptr;
-  int32_t* status = nullptr;
   uint32_t* ctr = nullptr;
   float* gpart = nullptr;   // partial sums of split-K tiles
   auto free_all = [&]() {
     for (void* p : packed) if (p) (void)hipFree(p);
-    for (void* p : {(void*)xp, (void*)status, (void*)ctr, (void*)gpart}) if (p) (void)hipFree(p);
+    for (void* p : {(void*)xp, (void*)ctr, (void*)gpart}) if (p) (void)hipFree(p);
   };
   if (mfma) {
     packed.assign(n_copies, nullptr);
@@ -812,8 +826,8 @@ int fleet_gemm(int32_t B, int32_t K, int32_t N, const void* x, const void* const
     if (hipDeviceSynchronize() != hipSuccess) { free_all(); return FLEET_EHIP; }
   }
   if ((rc = upload_graph(&dg, nullptr, mfma ? (const void* const*)packed.data() : w_copies, info.n_xcd))) { free_all(); return rc; }
-  if ((rc = upload(&status, nullptr, dev::ST_WORDS * 4))) { free_all(); return rc; }
-  if ((rc = upload(&ctr, nullptr, (size_t)dg.ctr_words * 4))) { free_all(); return rc; }
+  const int set_words = ctr_set_words(&dg);
+  if ((rc = upload(&ctr, nullptr, ctr_block_bytes(set_words)))) { free_all(); return rc; }
   // one region of partial sums: 8 k-slices of the batch padded to whole tiles; one region
   // per XCD under the XCD-aware schedules
   const size_t gpart_bytes = (size_t)8 * ((B + MAX_TILE_ROWS - 1) / MAX_TILE_ROWS * MAX_TILE_ROWS) * N * 4;
@@ -821,11 +835,11 @@ int fleet_gemm(int32_t B, int32_t K, int32_t N, const void* x, const void* const
   dev::Params P;
   memset(&P, 0, sizeof(P));
   fill_graph_params(P, &dg, info);
-  P.ctr = ctr;
+  P.ctr_block = ctr; P.ctr_set_words = set_words;
   P.buf[BUF_GEMM_X] = mfma ? xp : (void*)x; P.buf[BUF_GEMM_Y] = y; P.buf[BUF_GPART] = gpart;
   P.gpart_xcd_bytes = sched_mode == FLEET_SCHED_UNAWARE ? 0 : (int32_t)gpart_bytes;
   P.n_iter = 1;
-  P.status = status; P.timeout_ticks = timeout_ticks_from_env(); P.n_xcd = info.n_xcd; P.flags = flags;
+  P.timeout_ticks = timeout_ticks_from_env(); P.n_xcd = info.n_xcd; P.flags = flags;
   P.batch = B; P.hidden = K;
   const int nm = n_marks(0);
   for (int xc = 0; xc < info.n_xcd; ++xc) { P.q_begin[xc] = dg.g.marks[(size_t)xc * nm + 0]; P.q_end[xc] = dg.g.marks[(size_t)xc * nm + nm - 1]; }
@@ -833,9 +847,8 @@ int fleet_gemm(int32_t B, int32_t K, int32_t N, const void* x, const void* const
   hipEvent_t e0 = nullptr, e1 = nullptr;
   hipError_t he = hipEventCreate(&e0);
   if (he == hipSuccess) he = hipEventCreate(&e1);
+  if (he == hipSuccess) he = hipMemsetAsync(ctr, 0, ctr_block_bytes(set_words), st);   // (synchronous call: never captured)
   if (he == hipSuccess) {
-    const int words = dg.ctr_words;
-    hipLaunchKernelGGL(fleet_reset_kernel, dim3((words + 255) / 256), dim3(256), 0, st, ctr, words, -1, 0u, status, 0, 1, 0, -1);
     (void)hipEventRecord(e0, st);
     int lrc = launch_persistent(&dg, P, info.n_cu, st);
     (void)hipEventRecord(e1, st);
@@ -843,13 +856,14 @@ int fleet_gemm(int32_t B, int32_t K, int32_t N, const void* x, const void* const
     if (he == hipSuccess) he = hipEventSynchronize(e1);
     if (he == hipSuccess && elapsed_ms) he = hipEventElapsedTime(elapsed_ms, e0, e1);
   }
-  int32_t code[dev::ST_WORDS] = {0};
-  if (he == hipSuccess) he = hipMemcpy(code, status, sizeof(code), hipMemcpyDeviceToHost);
+  fleet_status_t status;
+  memset(&status, 0, sizeof(status));
+  const int src = he == hipSuccess ? read_status(ctr, set_words, &status) : FLEET_OK;
   if (e0) (void)hipEventDestroy(e0);
   if (e1) (void)hipEventDestroy(e1);
   free_all();
   if (he != hipSuccess) { g_last_hip = (int)he; return FLEET_EHIP; }
-  return code[dev::ST_CODE];
+  return src ? src : status.code;
 }
 
 int fleet_copy(void* dst, const void* src, size_t bytes, void* stream) {

@@ -445,3 +445,39 @@ def test_timeout_is_reported_not_hung(monkeypatch):
         assert st["code"] in (0, -4)
     finally:
         F.fleet_destroy(f)
+
+
+@pytest.mark.parametrize("static", [False, True])
+def test_steps_after_an_aborted_one(static):
+    """The counters of a launch are cleared by the launch itself, also when it was aborted (here: a
+    position beyond the cache, which the kernel checks): steps of any batch bucket that follow on
+    the same handle equal those of a fresh one bit for bit, and the status reads ok again."""
+    sh = si.reduced_shape(max_batch=40, max_seq=96, n_layers=2, vocab=512)
+    entry = F.fleet_decode_step_static if static else F.fleet_decode_step
+    sizes = (1, 3, 12) if static else (1, 3, 12, 40)
+    m = Model(sh, seed=81, batch=40, positions=np.random.default_rng(81).integers(0, 96, 40).astype(np.int32))
+    stream = torch.cuda.current_stream().cuda_stream
+
+    def step(f, batch, pos):
+        hout = torch.zeros((batch, sh.hidden), device="cuda", dtype=torch.float32)
+        logits = torch.zeros((batch, sh.vocab), device="cuda", dtype=torch.float32)
+        entry(f, batch, m.hidden, None, m.kc.clone(), m.vc.clone(), pos, hout, logits, stream)
+        return F.fleet_last_status(f)["code"], hout, logits
+
+    f, fresh = (F.fleet_create(sh.asdict(), m.w, 0, 0, 0) for _ in range(2))
+    try:
+        ref = {b: F.fleet_decode_step(fresh, b, m.hidden, None, m.kc.clone(), m.vc.clone(), m.pos, h, lg, stream) or (h, lg)
+               for b in sizes for h, lg in [(torch.zeros((b, sh.hidden), device="cuda"), torch.zeros((b, sh.vocab), device="cuda"))]}
+        assert F.fleet_last_status(fresh)["code"] == 0
+        for bad_batch in sizes:
+            bad = m.pos.clone()
+            bad[bad_batch - 1] = sh.max_seq
+            print(f"aborted step of batch {bad_batch}", flush=True)
+            assert step(f, bad_batch, bad)[0] == -1
+            for b in sizes:
+                code, hout, logits = step(f, b, m.pos)
+                assert code == 0
+                assert torch.equal(hout, ref[b][0]) and torch.equal(logits, ref[b][1]), (bad_batch, b)
+    finally:
+        F.fleet_destroy(f)
+        F.fleet_destroy(fresh)
