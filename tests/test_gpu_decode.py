@@ -136,6 +136,45 @@ def test_attention_scores_of_wide_range(batch, ramp):
         check_new_kv(m, got[2], got[3], k, v)
 
 
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("grp", [1, 2, 3, 4])
+def test_attention_key_counts_at_the_edges_of_a_step(grp, paged):
+    """Attention reads groups of four keys, two groups 32 keys apart per wavefront and step of 64 keys:
+    cache lengths around those edges, for 1 to 4 query heads per kv head, batch 1 (FMA-path kernel) and 16 (MFMA-path
+    kernel).  The output projection is scaled so that the attention output makes up nearly all of the
+    result; the 2e-2 x RMS bar leaves the bf16 rounding of the attention output (2^-9) five-fold room."""
+    lengths = [0, 1, 3, 4, 5, 31, 32, 33, 36, 63, 64, 65, 127, 128, 129, 255]
+    sh = si.Shape(1, 1024, 2 * grp, 2, 128, 1024, 0, len(lengths), 256)
+    m = Model(sh, seed=60 + grp, batch=len(lengths), positions=lengths)
+    m.w["wo"][0].mul_(100.0)
+    m.w_host = si.weights_to_host(m.w)
+    (ho, _), k, v = m.run_oracle()
+    page, per = 64, 4
+    table = torch.randperm(per * len(lengths), generator=torch.Generator().manual_seed(grp)).to(torch.int32).view(-1, per)
+    pool = [torch.zeros((1, table.numel(), 2, page, 128), dtype=c.dtype, device="cuda") for c in (m.kc, m.vc)]
+    for b in range(len(lengths)):
+        for i in range(per):
+            for src, dst in zip((m.kc, m.vc), pool):
+                dst[0, int(table[b, i])] = src[0, b, :, page * i:page * (i + 1)]
+    f = F.fleet_create(sh.asdict(), m.w, 0, 0, 0)
+    try:
+        for rows in [slice(0, len(lengths))] + [slice(i, i + 1) for i in range(len(lengths))]:
+            n = rows.stop - rows.start
+            print(f"grp {grp} paged {paged} lengths {lengths[rows]}", flush=True)
+            hout = torch.full((n, sh.hidden), float("nan"), device="cuda", dtype=torch.float32)
+            if paged:
+                F.fleet_decode_step_paged(f, n, m.hidden[rows], None, pool[0].clone(), pool[1].clone(), table[rows].contiguous().cuda(),
+                                          page, table.numel(), per, m.pos[rows].contiguous(), hout, None)
+            else:   # (one row: its cache lies where the cache of row 0 is expected)
+                kc, vc = (torch.cat([c[:, rows], c[:, n:]], 1).contiguous() for c in (m.kc, m.vc))
+                F.fleet_decode_step(f, n, m.hidden[rows], None, kc, vc, m.pos[rows].contiguous(), hout, None)
+            st = F.fleet_last_status(f)
+            assert st["code"] == 0, st
+            assert_close(hout.cpu().numpy(), ho[rows], f"hidden_out of lengths {lengths[rows]}")
+    finally:
+        F.fleet_destroy(f)
+
+
 def test_misaligned_buffers_are_rejected():
     """Outputs are written in 16-byte pieces: a logits or hidden_out pointer that is not
     16-byte aligned is refused on the host before anything is launched."""
