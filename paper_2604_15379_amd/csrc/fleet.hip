@@ -36,7 +36,10 @@ FLEET_EXTERN_VARIANT(4) FLEET_EXTERN_VARIANT(5) FLEET_EXTERN_VARIANT(6)
 constexpr size_t STATIC_SET_WORDS = ((size_t)dev::C_EVENTS + (size_t)dev::ECACHE * (1 + dev::MAX_XCD) + dev::N_PAIR +
                                      (size_t)dev::COPY_GROUPS * dev::MAX_XCD * dev::ECACHE + dev::GEMM_CNT_WORDS + 31) / 32 * 32;
 constexpr size_t STATIC_CTR_BYTES = ((dev::CTR_HEAD + 2 * STATIC_SET_WORDS) * 4 + 255) / 256 * 256;
-static __device__ __align__(256) unsigned char fleet_static_scratch[STATIC_CTR_BYTES + FLEET_STATIC_SCRATCH_BYTES];
+// Behind the step's working memory: the attention pieces of a plan (4 query heads per kv head at most).
+constexpr size_t PIECE_SLOTS = (size_t)dev::MAX_XCD * dev::PLAN_WORKERS * 2;
+constexpr size_t PIECE_BYTES = PIECE_SLOTS * 4 * dev::PART_STRIDE * 4;
+static __device__ __align__(256) unsigned char fleet_static_scratch[STATIC_CTR_BYTES + FLEET_STATIC_SCRATCH_BYTES + PIECE_BYTES];
 
 namespace {
 
@@ -57,6 +60,7 @@ struct DevInfo {
 struct Work {
   float* x = nullptr; void* n = nullptr; float* qkv = nullptr; void* att = nullptr; void* h = nullptr;
   float* part = nullptr; float* gpart = nullptr; float* gu32 = nullptr;
+  float* piece = nullptr;    // partial results of the attention pieces of a plan
   float* ss = nullptr;       // sums of squares of the residual rows, per 16 features
   uint32_t* ctr_block = nullptr; int ctr_set_words = 0;
   size_t gpart_region = 0;   // bytes between the per-XCD regions of gpart
@@ -299,6 +303,7 @@ size_t ctr_block_bytes(int set_words) { return align_up((dev::CTR_HEAD + 2 * (si
 // graphs and its sets hold the largest graph's counters (the next launch may run any of them)
 void own_work(const fleet* f, const DevGraph* dg, Work* w) {
   work_layout(f, dg, f->work + f->ctr_bytes, w);
+  w->piece = (float*)(f->work + f->ctr_bytes + f->work_bytes);
   w->ctr_block = (uint32_t*)f->work;
   w->ctr_set_words = f->ctr_set_words;
 }
@@ -396,7 +401,10 @@ int upload_graph(DevGraph* dg, const fleet* f, const void* const* gemm_copies, i
     for (int qi = g.qoff[x]; qi < g.qoff[x + 1]; ++qi) {
       const int32_t* e = &g.qents[(size_t)qi * QENT_WORDS];
       if (e[Q_DIST] != D_XCD_RR && e[Q_DIST] != D_XCD_RR_TOP) continue;
-      for (int t = e[Q_FIRST]; t < e[Q_FIRST] + e[Q_COUNT]; ++t) fat[(size_t)t * dev::FAT_WORDS + dev::FAT_GROUP] = e[Q_COUNT];
+      for (int t = e[Q_FIRST]; t < e[Q_FIRST] + e[Q_COUNT]; ++t) {
+        fat[(size_t)t * dev::FAT_WORDS + dev::FAT_GROUP] = e[Q_COUNT];
+        fat[(size_t)t * dev::FAT_WORDS + dev::FAT_POS] = t - e[Q_FIRST];
+      }
     }
   if ((rc = upload(&dg->fat, fat.data(), fat.size() * 4))) return rc;
   // counter block: G[e], L[x][e], one arrival counter per (sequence, kv head) for the split-KV
@@ -459,6 +467,7 @@ int run_layers(fleet* f, const StepArgs& a, hipStream_t st) {
     int rc = static_workspace(&base);   // looked up by fleet_create on this device: a table read here
     if (rc) return rc;
     work_layout(f, dg, (char*)base + STATIC_CTR_BYTES, &w);
+    w.piece = (float*)((char*)base + STATIC_CTR_BYTES + FLEET_STATIC_SCRATCH_BYTES);
     w.ctr_block = (uint32_t*)base;
     w.ctr_set_words = (int)STATIC_SET_WORDS;
   } else {
@@ -471,6 +480,7 @@ int run_layers(fleet* f, const StepArgs& a, hipStream_t st) {
   P.ctr_block = w.ctr_block; P.ctr_set_words = w.ctr_set_words;
   P.buf[BUF_X] = w.x; P.buf[BUF_N] = w.n; P.buf[BUF_QKV] = w.qkv; P.buf[BUF_ATT] = w.att; P.buf[BUF_H] = w.h;
   P.buf[BUF_PART] = w.part; P.buf[BUF_GPART] = w.gpart; P.buf[BUF_GU32] = w.gu32; P.buf[BUF_SS] = w.ss;
+  P.buf[BUF_PIECE] = w.piece;
   P.buf[BUF_HIDDEN_IN] = (void*)a.hidden_in; P.buf[BUF_TOKENS] = (void*)a.tokens;
   P.buf[BUF_KC] = a.k_cache; P.buf[BUF_VC] = a.v_cache; P.buf[BUF_POS] = (void*)a.positions;
   P.buf[BUF_HIDDEN_OUT] = a.hidden_out; P.buf[BUF_LOGITS] = a.logits; P.buf[BUF_TOKENS_OUT] = a.tokens_out;
@@ -479,6 +489,13 @@ int run_layers(fleet* f, const StepArgs& a, hipStream_t st) {
   if (a.paging) {
     P.buf[BUF_PT] = (void*)a.paging->table;
     P.page_size = a.paging->page_size; P.n_pages = a.paging->n_pages; P.pt_stride = a.paging->stride;
+  }
+  // attention by plan: under the XCD-aware schedules
+  if (dev::variant_plans(variant_for(g.header[H_PATH], g.header[H_BATCH], g.header[H_TILE_M])) &&
+      f->shape.sched_mode != FLEET_SCHED_UNAWARE &&
+      (g.header[H_BATCH] * f->shape.n_kv_heads + nx - 1) / nx <= dev::PLAN_PAIRS) {
+    P.plan_batch = g.header[H_BATCH];
+    P.plan_splits = std::max(1, g.header[H_N_SPLITS]);
   }
   P.trace_cap = TRACE_CAP;
   // (no trace of a multi-step launch: the record area holds one step)
@@ -631,7 +648,7 @@ int fleet_create(const fleet_shape_t* shape, const fleet_weights_t* w, fleet_t**
       (loop ? f->graphs_loop : f->graphs).push_back(std::move(dg));
     }
   f->ctr_bytes = ctr_block_bytes(f->ctr_set_words);
-  if ((rc = upload(&f->work, nullptr, f->ctr_bytes + f->work_bytes))) return rc;
+  if ((rc = upload(&f->work, nullptr, f->ctr_bytes + f->work_bytes + PIECE_BYTES))) return rc;   // (work_bytes is a multiple of 256)
   HIP_TRY(hipMemset(f->work, 0, f->ctr_bytes));
   if ((rc = warm_kernels(f.get()))) return rc;
   {   // what fleet_last_status reads before the first step

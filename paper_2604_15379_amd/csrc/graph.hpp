@@ -56,6 +56,7 @@ enum Buf {
   BUF_NONE = 0, BUF_X, BUF_N, BUF_QKV, BUF_ATT, BUF_H, BUF_PART, BUF_HIDDEN_IN, BUF_TOKENS,
   BUF_KC, BUF_VC, BUF_POS, BUF_HIDDEN_OUT, BUF_LOGITS, BUF_GEMM_X, BUF_GEMM_Y, BUF_GPART, BUF_GU32, BUF_TOKENS_OUT, BUF_PT,
   BUF_SS,   // fp32 [batch][hidden / 16]: sums of squares of the residual stream, one per row and 16 features
+  BUF_PIECE,   // fp32 partial results of the attention pieces of a plan: two per worker of an XCD, a region per XCD
   N_BUF
 };
 

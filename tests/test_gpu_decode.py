@@ -175,6 +175,83 @@ def test_attention_key_counts_at_the_edges_of_a_step(grp, paged):
         F.fleet_destroy(f)
 
 
+def _plan_lengths(batch, seed):
+    """Very unequal cache lengths (a few long ones, many short, empty ones, edges of 64-key units)."""
+    rng = np.random.default_rng(seed)
+    pos = rng.integers(0, 90, batch)
+    pos[rng.permutation(batch)[:max(2, batch // 6)]] = rng.integers(400, 700, max(2, batch // 6))
+    edges = [0, 63, 64, 65, 128, 699]
+    pos[:len(edges)] = edges
+    return pos.astype(np.int32)
+
+
+@pytest.mark.parametrize("nq,nkv", [(1, 1), (6, 3), (8, 2), (8, 8)])
+@pytest.mark.parametrize("batch,tile_m,sched", [(17, 0, 0), (32, 0, 0), (33, 0, 0), (64, 32, 2), (100, 0, 0), (128, 0, 0)])
+def test_attention_by_plan_of_unequal_lengths(nq, nkv, batch, tile_m, sched):
+    """32- and 64-row tiles: the keys of an XCD are dealt to its workers by the lengths.  Whole workers per pair,
+    pairs laid end to end, more kv heads than XCDs and fewer, contiguous and paged cache, and a handle
+    that is made for more sequences than the step has; equal to the oracle, and a traced launch (which runs
+    every task of the graph) equal to the untraced one bit for bit.  (Output projection scaled as in the test above.)"""
+    sh = si.Shape(1, 512, nq, nkv, 128, 512, 0, batch, 700)
+    pos = _plan_lengths(batch, batch + nkv)
+    m = Model(sh, seed=70 + nq + nkv, batch=batch, positions=pos)
+    m.w["wo"][0].mul_(100.0)
+    m.w_host = si.weights_to_host(m.w)
+    (ho, _), k, v = m.run_oracle()
+    print(f"plan nq {nq} nkv {nkv} batch {batch} tile_m {tile_m} sched {sched}", flush=True)
+    got = m.run_gpu(sched, tile_m)
+    assert_close(got[0], ho, "hidden_out")
+    check_new_kv(m, got[2], got[3], k, v)
+    traced = m.run_gpu(sched, tile_m, F.FLAG_TRACE)
+    assert np.array_equal(traced[0], got[0])
+    page, per = 64, 11
+    n = batch - 3 if batch > 32 else batch     # (the graph for the whole batch serves it)
+    table = torch.randperm(per * n, generator=torch.Generator().manual_seed(batch)).to(torch.int32).view(n, per)
+    pool = [torch.zeros((1, per * n, nkv, page, 128), dtype=c.dtype, device="cuda") for c in (m.kc, m.vc)]
+    for src, dst in zip((m.kc, m.vc), pool):
+        for i in range(per):
+            part = src[0, :n, :, page * i:page * (i + 1)]
+            dst[0, table[:, i].long().cuda(), :, :part.shape[2]] = part
+    f = F.fleet_create(sh.asdict(), m.w, sched, tile_m, 0)
+    hout = torch.full((n, sh.hidden), float("nan"), device="cuda", dtype=torch.float32)
+    print("  paged", flush=True)
+    F.fleet_decode_step_paged(f, n, m.hidden[:n], None, pool[0], pool[1], table.cuda(), page, per * n, per, m.pos[:n].contiguous(), hout, None)
+    st = F.fleet_last_status(f)
+    F.fleet_destroy(f)
+    assert st["code"] == 0, st
+    assert_close(hout.cpu().numpy(), ho[:n], "hidden_out, paged")
+
+
+def test_plan_is_kept_over_the_steps_of_a_launch():
+    """One launch of 70 greedy steps (a plan serves 64) equals 70 launches of one: a head whose row t + 1 is the
+    embedding's row t makes the next token certain, the last hidden states agree to the parity bar."""
+    batch, n_tokens = 20, 70
+    sh = si.reduced_shape(max_batch=batch, max_seq=900, n_layers=1, vocab=1024)
+    pos = np.minimum(_plan_lengths(batch, 5), 900 - n_tokens - 1).astype(np.int32)
+    m = Model(sh, seed=91, batch=batch, positions=pos, with_embed=True)
+    m.w["lm_head"] = (m.w["embed"].roll(1, 0).float() * 0.05).to(torch.bfloat16)
+    f = F.fleet_create(sh.asdict(), m.w, 0, 0, 0)
+    res = []
+    try:
+        for calls in (1, n_tokens):
+            print(f"{n_tokens} tokens in {calls} launches", flush=True)
+            kc, vc, cur = m.kc.clone(), m.vc.clone(), m.pos.clone()
+            tok = torch.arange(batch, device="cuda", dtype=torch.int32) * 7
+            outs, hout = [], torch.zeros((batch, sh.hidden), device="cuda")
+            logits = torch.zeros((batch, sh.vocab), device="cuda")
+            for _ in range(calls):
+                out = torch.full((n_tokens // calls, batch), -1, device="cuda", dtype=torch.int32)
+                F.fleet_decode_tokens(f, batch, tok, kc, vc, cur, n_tokens // calls, out, hout, logits)
+                outs.append(out)
+            assert F.fleet_last_status(f)["code"] == 0
+            assert np.array_equal(cur.cpu().numpy(), pos + n_tokens)
+            res.append((torch.cat(outs).cpu().numpy(), hout.cpu().numpy()))
+    finally:
+        F.fleet_destroy(f)
+    assert np.array_equal(res[0][0], res[1][0])
+    assert_close(res[0][1], res[1][1], "hidden_out of the last step")
+
+
 def test_misaligned_buffers_are_rejected():
     """Outputs are written in 16-byte pieces: a logits or hidden_out pointer that is not
     16-byte aligned is refused on the host before anything is launched."""
