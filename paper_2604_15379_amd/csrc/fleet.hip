@@ -246,7 +246,6 @@ struct fleet {
   long long timeout_ticks = 0;
   const uint32_t* last_ctr_block = nullptr;   // counter block of the last launch (device)
   int last_set_words = 0;
-  float* last_x = nullptr;          // residual stream of the last launch (device)
 
   ~fleet() {
     for (void* p : {(void*)work, (void*)rope, (void*)trace})
@@ -449,8 +448,7 @@ struct StepArgs {
   bool static_ws = false;                            // work in the static workspace
 };
 
-// No allocation, no host-device copy, no synchronisation: kernels (and, for layer ranges,
-// device-to-device copies) on the stream only.
+// No allocation, no copy, no synchronisation: kernels on the stream only.
 int run_layers(fleet* f, const StepArgs& a, hipStream_t st) {
   // the kernels move activations, cache rows and logits in 16-byte pieces
   for (const void* p : {a.hidden_in, (const void*)a.k_cache, (const void*)a.v_cache, (const void*)a.hidden_out, (const void*)a.logits})
@@ -504,22 +502,23 @@ int run_layers(fleet* f, const StepArgs& a, hipStream_t st) {
   P.nq = f->shape.n_q_heads; P.nkv = f->shape.n_kv_heads; P.hd = f->shape.head_dim; P.max_batch = f->shape.max_batch;
   P.max_seq = f->shape.max_seq; P.hidden = f->shape.hidden; P.ffn = f->shape.ffn; P.batch = a.batch; P.eps = f->shape.rms_eps; P.vocab = f->shape.vocab;
   // marks of a queue: ingest, layer 0 .. L-1, final stage, LM head, end.  The final stage
-  // (hidden_out, final norm) runs whenever asked for; the LM head only with a logits buffer.
+  // (hidden_out, final norm) and the LM head run with a logits buffer; without one the last layer's down
+  // projection stores hidden_out itself (a trace of a whole step shows the final stage all the same).
+  const bool final_stage = a.with_final && (a.logits || P.trace);
   const int mb = a.with_ingest ? 0 : 1 + a.layer_begin;
-  const int me = !a.with_final ? 1 + a.layer_end : (a.logits ? L + 3 : L + 2);
+  const int me = !final_stage ? 1 + a.layer_end : (a.logits ? L + 3 : L + 2);
+  P.direct_out = final_stage ? 0 : a.layer_end;
   for (int x = 0; x < nx; ++x) {
     P.q_begin[x] = g.marks[(size_t)x * nm + mb];
     P.q_end[x] = g.marks[(size_t)x * nm + me];
   }
   if (a.x_in) {   // a residual stream from the caller: copy it in, with the sums of squares its first consumer needs
-    HIP_TRY(hipMemcpyAsync(w.x, a.x_in, (size_t)a.batch * f->shape.hidden * 4, hipMemcpyDeviceToDevice, st));
-    hipLaunchKernelGGL(fleet_row_ss_kernel, dim3(std::max(1, a.batch * (f->shape.hidden / 16) / 256)), dim3(256), 0, st,
-                       (const float*)w.x, w.ss, a.batch, f->shape.hidden);
+    const int n = a.batch * f->shape.hidden;
+    hipLaunchKernelGGL(fleet_stream_in_kernel, dim3((n / 4 + 255) / 256), dim3(256), 0, st, a.x_in, w.x, w.ss, n);
   }
   if (!a.with_ingest) P.preset_event = g.xready[a.layer_begin];
   f->last_ctr_block = w.ctr_block;
   f->last_set_words = w.ctr_set_words;
-  f->last_x = w.x;
   return launch_persistent(dg, P, f->info.n_cu, st);
 }
 
@@ -654,7 +653,7 @@ int fleet_create(const fleet_shape_t* shape, const fleet_weights_t* w, fleet_t**
   {   // what fleet_last_status reads before the first step
     Work w0;
     own_work(f.get(), f->graphs[0].get(), &w0);
-    f->last_ctr_block = w0.ctr_block; f->last_set_words = w0.ctr_set_words; f->last_x = w0.x;
+    f->last_ctr_block = w0.ctr_block; f->last_set_words = w0.ctr_set_words;
   }
   if (shape->flags & (FLEET_FLAG_TRACE | FLEET_FLAG_TIMING))
     if ((rc = upload(&f->trace, nullptr, ((size_t)f->info.n_cu * TRACE_CAP * 8 + f->info.n_cu) * 4))) return rc;
@@ -718,7 +717,6 @@ int fleet_decode_layers(fleet_t* f, int32_t batch, int32_t layer_begin, int32_t 
   a.k_cache = k_cache; a.v_cache = v_cache; a.positions = positions; a.hidden_out = x_out; a.logits = logits; a.x_in = x_in;
   int rc = run_layers(f, a, st);
   if (rc) return rc;
-  if (!a.with_final) HIP_TRY(hipMemcpyAsync(x_out, f->last_x, (size_t)batch * f->shape.hidden * 4, hipMemcpyDeviceToDevice, st));
   return FLEET_OK;
 }
 

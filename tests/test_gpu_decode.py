@@ -252,6 +252,31 @@ def test_plan_is_kept_over_the_steps_of_a_launch():
     assert_close(res[0][1], res[1][1], "hidden_out of the last step")
 
 
+@pytest.mark.parametrize("batch", [1, 3, 20, 40])
+def test_layer_range_on_a_callers_stream(batch):
+    """fleet_decode_layers on a caller's fp32 rows, in place, out of place and from rows aligned to 4 bytes only,
+    one layer after the other or both at once, against fleet_decode_step on the same (bf16) rows; the output comes from the last down
+    projection of the range (FMA epilogue, split-K and register-resident MFMA epilogues)."""
+    sh = si.reduced_shape(max_batch=batch, max_seq=96, n_layers=2)
+    m = Model(sh, seed=95, batch=batch, positions=np.random.default_rng(batch).integers(0, 96, batch).astype(np.int32))
+    ref = m.run_gpu()[0]
+    f = F.fleet_create(sh.asdict(), m.w, 0, 0, 0)
+    try:
+        x0 = m.hidden.float()
+        for ranges, in_place, shift in (([(0, 2)], True, 0), ([(0, 2)], False, 1), ([(0, 1), (1, 2)], True, 0)):
+            print(f"layer range batch={batch} {ranges} in_place={in_place} shift={shift}", flush=True)
+            kc, vc = m.kc.clone(), m.vc.clone()
+            x = torch.zeros(x0.numel() + 4, device="cuda")[shift:shift + x0.numel()].view_as(x0)
+            x.copy_(x0)
+            out = x if in_place else torch.full_like(x0, float("nan"))
+            for lo, hi in ranges:
+                F.fleet_decode_layers(f, batch, lo, hi, x, kc, vc, m.pos, out, None)
+            assert F.fleet_last_status(f)["code"] == 0
+            assert_close(out.cpu().numpy(), ref, "x_out")
+    finally:
+        F.fleet_destroy(f)
+
+
 def test_misaligned_buffers_are_rejected():
     """Outputs are written in 16-byte pieces: a logits or hidden_out pointer that is not
     16-byte aligned is refused on the host before anything is launched."""
