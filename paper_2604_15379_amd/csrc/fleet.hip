@@ -296,6 +296,12 @@ size_t work_layout(const fleet* f, const DevGraph* dg, char* base, Work* w) {
   return off;
 }
 
+// attention by plan: the kernels that can, under the XCD-aware schedules
+bool can_plan(const fleet* f, const DevGraph* dg) {
+  const int32_t* h = dg->g.header.data();
+  return dev::variant_plans(variant_for(h[H_PATH], h[H_BATCH], h[H_TILE_M])) && f->shape.sched_mode != FLEET_SCHED_UNAWARE &&
+         (h[H_BATCH] * f->shape.n_kv_heads + f->info.n_xcd - 1) / f->info.n_xcd <= dev::PLAN_PAIRS;
+}
 int ctr_set_words(const DevGraph* dg) { return (dg->ctr_words + 31) / 32 * 32; }
 size_t ctr_block_bytes(int set_words) { return align_up((dev::CTR_HEAD + 2 * (size_t)set_words) * 4); }
 // the fleet's own working memory for graph dg: the counter block sits at the same place for all
@@ -488,10 +494,7 @@ int run_layers(fleet* f, const StepArgs& a, hipStream_t st) {
     P.buf[BUF_PT] = (void*)a.paging->table;
     P.page_size = a.paging->page_size; P.n_pages = a.paging->n_pages; P.pt_stride = a.paging->stride;
   }
-  // attention by plan: under the XCD-aware schedules
-  if (dev::variant_plans(variant_for(g.header[H_PATH], g.header[H_BATCH], g.header[H_TILE_M])) &&
-      f->shape.sched_mode != FLEET_SCHED_UNAWARE &&
-      (g.header[H_BATCH] * f->shape.n_kv_heads + nx - 1) / nx <= dev::PLAN_PAIRS) {
+  if (can_plan(f, dg)) {
     P.plan_batch = g.header[H_BATCH];
     P.plan_splits = std::max(1, g.header[H_N_SPLITS]);
   }
@@ -505,7 +508,13 @@ int run_layers(fleet* f, const StepArgs& a, hipStream_t st) {
   // (hidden_out, final norm) and the LM head run with a logits buffer; without one the last layer's down
   // projection stores hidden_out itself (a trace of a whole step shows the final stage all the same).
   const bool final_stage = a.with_final && (a.logits || P.trace);
-  const int mb = a.with_ingest ? 0 : 1 + a.layer_begin;
+  // No ingest stage (but in a trace) where the first op of layer 0 is a norm stage, or a GEMV that normalises its
+  // input itself: they take the input rows, and the ingest event counts as complete.
+  const int32_t* op1 = &g.ops[OP_WORDS];
+  P.direct_in = a.with_ingest && !P.trace &&
+                (op1[O_BODY] == B_RMSNORM || (op1[O_BODY] == B_GEMM && op1[O_PATH] == P_FMA && ((op1[O_AUX2] >> 8) & 3) == X_LDS_NORM));
+  P.embed = f->embed;
+  const int mb = a.with_ingest && !P.direct_in ? 0 : 1 + a.layer_begin;
   const int me = !final_stage ? 1 + a.layer_end : (a.logits ? L + 3 : L + 2);
   P.direct_out = final_stage ? 0 : a.layer_end;
   for (int x = 0; x < nx; ++x) {
@@ -516,7 +525,7 @@ int run_layers(fleet* f, const StepArgs& a, hipStream_t st) {
     const int n = a.batch * f->shape.hidden;
     hipLaunchKernelGGL(fleet_stream_in_kernel, dim3((n / 4 + 255) / 256), dim3(256), 0, st, a.x_in, w.x, w.ss, n);
   }
-  if (!a.with_ingest) P.preset_event = g.xready[a.layer_begin];
+  if (!a.with_ingest || P.direct_in) P.preset_event = g.xready[a.layer_begin];
   f->last_ctr_block = w.ctr_block;
   f->last_set_words = w.ctr_set_words;
   return launch_persistent(dg, P, f->info.n_cu, st);
@@ -647,7 +656,9 @@ int fleet_create(const fleet_shape_t* shape, const fleet_weights_t* w, fleet_t**
       (loop ? f->graphs_loop : f->graphs).push_back(std::move(dg));
     }
   f->ctr_bytes = ctr_block_bytes(f->ctr_set_words);
-  if ((rc = upload(&f->work, nullptr, f->ctr_bytes + f->work_bytes + PIECE_BYTES))) return rc;   // (work_bytes is a multiple of 256)
+  bool plans = false;
+  for (auto& dg : f->graphs) plans = plans || can_plan(f.get(), dg.get());
+  if ((rc = upload(&f->work, nullptr, f->ctr_bytes + f->work_bytes + (plans ? PIECE_BYTES : 0)))) return rc;   // (work_bytes is a multiple of 256)
   HIP_TRY(hipMemset(f->work, 0, f->ctr_bytes));
   if ((rc = warm_kernels(f.get()))) return rc;
   {   // what fleet_last_status reads before the first step

@@ -277,6 +277,39 @@ def test_layer_range_on_a_callers_stream(batch):
         F.fleet_destroy(f)
 
 
+@pytest.mark.parametrize("batch", [1, 2, 20, 40])
+@pytest.mark.parametrize("hidden", [1024, 4608])   # a row of one and of two passes of the norm
+def test_input_rows_from_token_ids_and_hidden_states(batch, hidden):
+    """A step from token ids equals, bit for bit, the step from the embedding's rows, with and without an ingest
+    stage in front (a traced launch has one); a token outside the vocabulary is reported."""
+    sh = si.Shape(1, hidden, 8, 2, 128, 1024, 512, batch, 96)
+    m = Model(sh, seed=97, batch=batch, positions=np.random.default_rng(batch).integers(0, 96, batch).astype(np.int32), with_embed=True)
+    ids = torch.tensor(np.random.default_rng(1).integers(0, 512, batch).astype(np.int32), device="cuda")
+    rows = m.w["embed"][ids.long()].contiguous()
+    stream = torch.cuda.current_stream().cuda_stream
+
+    def step(flags, x, tok, want_logits):
+        f = F.fleet_create(sh.asdict(), m.w, 0, 0, flags)
+        hout = torch.full((batch, hidden), float("nan"), device="cuda")
+        logits = torch.zeros((batch, 512), device="cuda") if want_logits else None
+        F.fleet_decode_step(f, batch, x, tok, m.kc.clone(), m.vc.clone(), m.pos, hout, logits, stream)
+        code = F.fleet_last_status(f)["code"]
+        F.fleet_destroy(f)
+        return code, hout
+
+    print(f"input rows batch={batch} hidden={hidden}", flush=True)
+    code, ref = step(F.FLAG_TRACE, rows, None, True)
+    assert code == 0 and torch.isfinite(ref).all()
+    for x, tok in ((rows, None), (None, ids)):
+        for want_logits in (False, True):
+            code, got = step(0, x, tok, want_logits)
+            assert code == 0 and torch.equal(got, ref)
+    for bad in (-1, 512):
+        tok = ids.clone()
+        tok[batch - 1] = bad
+        assert step(0, None, tok, True)[0] == -1
+
+
 def test_misaligned_buffers_are_rejected():
     """Outputs are written in 16-byte pieces: a logits or hidden_out pointer that is not
     16-byte aligned is refused on the host before anything is launched."""
