@@ -310,6 +310,24 @@ def test_input_rows_from_token_ids_and_hidden_states(batch, hidden):
         assert step(0, None, tok, True)[0] == -1
 
 
+@pytest.mark.parametrize("batch", [1, 2, 16, 20])
+@pytest.mark.parametrize("hidden", [4160, 8192])
+def test_hidden_sizes_above_4096(batch, hidden):
+    """The norm that the GEMMs of 16-row tiles apply themselves takes its sums of squares and gains in pieces of 4096
+    features; gains far from one, so that a missed piece shows.  (The share of bit-equal
+    cache entries that check_new_kv asks for was set for sums over at most 4096 products.)"""
+    sh = si.Shape(1, hidden, 8, 2, 128, 512, 512, batch, 64)
+    m = Model(sh, seed=98, batch=batch, positions=np.random.default_rng(batch).integers(0, 64, batch).astype(np.int32))
+    for name in ("ln1", "ln2"):
+        m.w[name][0].copy_(torch.linspace(0.5, 2.0, hidden, device="cuda"))
+    m.w_host = si.weights_to_host(m.w)
+    print(f"hidden={hidden} batch={batch}", flush=True)
+    (ho, lg), _, _ = m.run_oracle()
+    got = m.run_gpu()
+    assert_close(got[0], ho, "hidden_out")
+    assert_close(got[1], lg, "logits")
+
+
 def test_misaligned_buffers_are_rejected():
     """Outputs are written in 16-byte pieces: a logits or hidden_out pointer that is not
     16-byte aligned is refused on the host before anything is launched."""
