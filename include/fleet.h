@@ -170,7 +170,10 @@ int fleet_create(const fleet_shape_t *shape, const fleet_weights_t *weights, fle
  * hidden_in, the caches, hidden_out and logits must be 16-byte aligned (FLEET_EINVAL
  * otherwise): the kernels move them in 16-byte pieces.
  * The call launches one kernel on `stream` and does nothing else: no allocation, no
- * copy, no synchronisation (it can be captured into a HIP graph).
+ * copy, no synchronisation (it can be captured into a HIP graph).  From a handle's first call on
+ * another stream than the default one on, each call launches a small kernel that clears the
+ * dependency counters in front: calls on one handle must not overlap, but where two streams
+ * did overlap all the same, their steps are lost and the next one is right again.
  * A dependency wait that times out aborts the step on the device; the next
  * fleet_last_status() reports FLEET_ETIMEOUT.
  * The result is a function of the inputs alone: every reduction has a fixed order, so
@@ -206,8 +209,9 @@ int fleet_destroy(fleet_t *f);
  * are bit-identical to it.  A step whose working memory exceeds the array (large batches on
  * the MFMA path with split-K partial sums; the Qwen3-8B shape fits up to batch 16) is
  * refused with FLEET_ETOOBIG before anything is launched.  The call itself allocates
- * nothing, frees nothing and copies nothing from the host; every launch leaves the counters
- * cleared for the next one.  All calls on one GPU share the array: calls
+ * nothing, frees nothing and copies nothing from the host; the counters are cleared as for
+ * fleet_decode_step (by the launch before, or by a kernel in front once the array has been used on
+ * another stream than the default one).  All calls on one GPU share the array: calls
  * that overlap on one GPU (two streams, two fleets, two threads) race; calls on one stream
  * are safe.  fleet_last_status reports on the last step launched either way.
  */
@@ -303,8 +307,17 @@ int fleet_graph_dump(fleet_t *f, int32_t batch, void *buf, size_t *len);
  */
 int fleet_trace_read(fleet_t *f, void *buf, size_t *len);
 
-/* fleet_last_status: synchronise the device and report the last step's outcome. */
+/* fleet_last_status: synchronise the device and report the last step's outcome.  A step that did
+ * not get all its workers (the counters were not clean: steps had overlapped) is reported as
+ * FLEET_ETIMEOUT; the call then also cleans the counters for the next step. */
 int fleet_last_status(fleet_t *f, fleet_status_t *out);
+
+/*
+ * fleet_test_counter (test): synchronise the device and store `value` in word `word` of the dependency
+ * counters -- of the handle, or (static_block != 0) of the array of fleet_decode_step_static -- as a
+ * step that another one disturbed may leave it.  set 0: the counters the next step works on; 1: the other ones.
+ */
+int fleet_test_counter(fleet_t *f, int32_t static_block, int32_t set, int32_t word, uint32_t value);
 
 /*
  * fleet_device_probe: XCD id (hardware XCC_ID) of each of n_blocks workgroups of

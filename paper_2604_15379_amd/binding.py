@@ -28,7 +28,7 @@ EXPORTS = (
     "fleet_graph_build", "fleet_graph_dump", "fleet_trace_read", "fleet_last_status",
     "fleet_device_probe", "fleet_copy", "fleet_weight_bytes", "fleet_weight_bytes_per_xcd",
     "fleet_l2_window_bytes", "fleet_l2_hit_model", "fleet_effective_intensity",
-    "fleet_step_bytes", "fleet_strerror",
+    "fleet_step_bytes", "fleet_strerror", "fleet_test_counter",
 )
 
 
@@ -247,6 +247,13 @@ def fleet_device_probe(n_blocks: int) -> np.ndarray:
     if rc != 0:
         raise FleetError(rc, "fleet_device_probe")
     return out
+
+
+def fleet_test_counter(f: Fleet, static_block: bool, which_set: int, word: int, value: int) -> None:
+    rc = load_library().fleet_test_counter(f.handle, C.c_int32(static_block), C.c_int32(which_set), C.c_int32(word),
+                                           C.c_uint32(value))
+    if rc != 0:
+        raise FleetError(rc, "fleet_test_counter")
 
 
 def fleet_copy(dst, src, nbytes: int, stream=0) -> None:

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -146,6 +147,7 @@ int launch_persistent(DevGraph* dg, dev::Params& P, int n_cu, hipStream_t st) {
 std::mutex g_dev_mutex;
 bool g_prepared[MAX_DEVICES] = {false};
 void* g_static_ws[MAX_DEVICES] = {nullptr};
+std::atomic<bool> g_static_any_stream[MAX_DEVICES];   // the array's counter block, as fleet::any_stream
 
 int prepare_kernel() {
   int dev_id = 0, lds = 0;
@@ -169,7 +171,7 @@ int prepare_kernel() {
 
 // Device address of the static workspace on the current device (every device holds its own
 // copy of the array at its own address); looked up once per device.
-int static_workspace(void** out) {
+int static_workspace(void** out, std::atomic<bool>** any_stream = nullptr) {
   int dev_id = 0;
   HIP_TRY(hipGetDevice(&dev_id));
   if (dev_id < 0 || dev_id >= MAX_DEVICES) return FLEET_EDEVICE;
@@ -181,6 +183,7 @@ int static_workspace(void** out) {
     g_static_ws[dev_id] = p;
   }
   *out = g_static_ws[dev_id];
+  if (any_stream) *any_stream = &g_static_any_stream[dev_id];
   return FLEET_OK;
 }
 
@@ -240,11 +243,12 @@ struct fleet {
   std::vector<std::unique_ptr<DevGraph>> graphs_loop;   // with the next-token stage (multi-step launches)
   char* work = nullptr;      // the fleet's own working memory: the counter block, then work_layout()
   int ctr_set_words = 0;
+  std::atomic<bool> any_stream{false};   // has a launch in `work` ever been on another stream than the default one?
   size_t ctr_bytes = 0, work_bytes = 0;
   float2* rope = nullptr;
   int32_t* trace = nullptr;
   long long timeout_ticks = 0;
-  const uint32_t* last_ctr_block = nullptr;   // counter block of the last launch (device)
+  uint32_t* last_ctr_block = nullptr;   // counter block of the last launch (device)
   int last_set_words = 0;
 
   ~fleet() {
@@ -317,15 +321,48 @@ void own_work(const fleet* f, const DevGraph* dg, Work* w) {
 size_t static_need(const fleet* f, const DevGraph* dg) {
   return work_layout(f, dg, nullptr, nullptr) + align_up(((size_t)dg->ctr_words - dev::C_EVENTS + 96) * 4) + 256;
 }
-// The outcome of the last launch that used the counter block, from its set (the head word already
-// names the other one): the first abort report, and the workers per XCD.
-int read_status(const uint32_t* block, int set_words, fleet_status_t* out) {
-  uint32_t set = 0, w[dev::C_READY];
+// Does a launch on `st` find its counters clean?  It works on what the launches before it left: a set that the last of
+// them has cleared while it worked on the other.  That holds where launches follow each other, and on the default
+// stream they do: nobody can capture, destroy or replace it.  Launches on other streams may overlap (which the callers are told not
+// to do), and then one clears what another still counts in, and what is left may be anything.  So from a block's
+// first launch on any other stream on, every launch has the counters cleared in front of it, in stream order, and is
+// right whatever happened before (the kernel in front: small one-layer step 32.1 -> 33.9 us, two 8B layers at batch 1 148.5 -> 150.2).
+bool clean_by_order(std::atomic<bool>* any_stream, hipStream_t st) {
+  if (st != nullptr) any_stream->store(true);
+  return !any_stream->load();
+}
+int clear_counters(const Work& w, const DevGraph* dg, hipStream_t st) {
+  u32x4* block = (u32x4*)w.ctr_block;
+  int n = dev::CTR_HEAD + dg->ctr_words;
+  void* args[] = {(void*)&block, (void*)&n};
+  HIP_TRY(hipLaunchKernel((const void*)fleet_reset_kernel, dim3((n / 4 + 256) / 256), dim3(256), args, 0, st));
+  return FLEET_OK;
+}
+// The outcome of the last launch that used the counter block, from its set: the first abort report, and the
+// workers per XCD.  The head word names the other set, clean for the next launch -- unless the launch never
+// got through its start-up (it found counters that an overlapping launch had left): then it is the launch's own,
+// and the change of sets is made up for here, so that the next launch starts clean.
+int read_status(uint32_t* block, int set_words, int n_workers, fleet_status_t* out) {
+  uint32_t set = 0, both[2][dev::C_READY];
   HIP_TRY(hipMemcpy(&set, block, sizeof(set), hipMemcpyDeviceToHost));
-  HIP_TRY(hipMemcpy(w, block + dev::CTR_HEAD + (size_t)((set & 1) ^ 1) * set_words, sizeof(w), hipMemcpyDeviceToHost));
+  set &= 1;
+  for (uint32_t i = 0; i < 2; ++i)
+    HIP_TRY(hipMemcpy(both[i], block + dev::CTR_HEAD + (size_t)i * set_words, sizeof(both[i]), hipMemcpyDeviceToHost));
+  auto workers = [](const uint32_t* w) {
+    uint32_t n = 0;
+    for (int x = 0; x < dev::MAX_XCD; ++x) n += w[dev::C_ROSTER + 32 * x];
+    return n;
+  };
+  if (workers(both[set]) != 0 || both[set][dev::C_ABORT] != 0) {
+    set ^= 1;
+    HIP_TRY(hipMemset(block + dev::CTR_HEAD + (size_t)set * set_words, 0, (size_t)set_words * 4));
+    HIP_TRY(hipMemcpy(block, &set, sizeof(set), hipMemcpyHostToDevice));
+    HIP_TRY(hipDeviceSynchronize());
+  }
+  const uint32_t* w = both[set ^ 1];
   const bool aborted = w[dev::C_ABORT] != 0;
   const uint32_t* rep = w + dev::C_REPORT;
-  out->code = aborted ? (int32_t)rep[0] : FLEET_OK;
+  out->code = aborted ? (int32_t)rep[0] : workers(w) == (uint32_t)n_workers ? FLEET_OK : FLEET_ETIMEOUT;
   out->task = aborted ? (int32_t)rep[1] : -1;
   out->event = aborted ? (int32_t)rep[2] : 0;
   out->observed = aborted ? (int32_t)rep[3] : 0;
@@ -465,10 +502,11 @@ int run_layers(fleet* f, const StepArgs& a, hipStream_t st) {
   if (!dg) return FLEET_EINVAL;
   const Graph& g = dg->g;
   Work w;
+  std::atomic<bool>* any_stream = &f->any_stream;
   if (a.static_ws) {
     if (static_need(f, dg) > (size_t)FLEET_STATIC_SCRATCH_BYTES) return FLEET_ETOOBIG;
     void* base = nullptr;
-    int rc = static_workspace(&base);   // looked up by fleet_create on this device: a table read here
+    int rc = static_workspace(&base, &any_stream);   // looked up by fleet_create on this device: a table read here
     if (rc) return rc;
     work_layout(f, dg, (char*)base + STATIC_CTR_BYTES, &w);
     w.piece = (float*)((char*)base + STATIC_CTR_BYTES + FLEET_STATIC_SCRATCH_BYTES);
@@ -528,6 +566,10 @@ int run_layers(fleet* f, const StepArgs& a, hipStream_t st) {
   if (!a.with_ingest || P.direct_in) P.preset_event = g.xready[a.layer_begin];
   f->last_ctr_block = w.ctr_block;
   f->last_set_words = w.ctr_set_words;
+  if (!clean_by_order(any_stream, st)) {
+    int rc = clear_counters(w, dg, st);
+    if (rc) return rc;
+  }
   return launch_persistent(dg, P, f->info.n_cu, st);
 }
 
@@ -763,12 +805,32 @@ int fleet_decode_tokens(fleet_t* f, int32_t batch, int32_t* tokens, void* k_cach
   return run_layers(f, a, (hipStream_t)stream);
 }
 
+int fleet_test_counter(fleet_t* f, int32_t static_block, int32_t set, int32_t word, uint32_t value) {
+  if (!f || set < 0 || set > 1 || word < 0) return FLEET_EINVAL;
+  uint32_t* block = (uint32_t*)f->work;
+  int set_words = f->ctr_set_words;
+  if (static_block) {
+    void* base = nullptr;
+    int rc = static_workspace(&base);
+    if (rc) return rc;
+    block = (uint32_t*)base;
+    set_words = (int)STATIC_SET_WORDS;
+  }
+  if (word >= set_words) return FLEET_EINVAL;
+  HIP_TRY(hipDeviceSynchronize());
+  uint32_t head = 0;
+  HIP_TRY(hipMemcpy(&head, block, sizeof(head), hipMemcpyDeviceToHost));
+  HIP_TRY(hipMemcpy(block + dev::CTR_HEAD + (size_t)((head & 1) ^ set) * set_words + word, &value, sizeof(value), hipMemcpyHostToDevice));
+  HIP_TRY(hipDeviceSynchronize());
+  return FLEET_OK;
+}
+
 int fleet_last_status(fleet_t* f, fleet_status_t* out) {
   if (!f || !out) return FLEET_EINVAL;
   memset(out, 0, sizeof(*out));
   hipError_t e = hipDeviceSynchronize();
   out->hip_error = e != hipSuccess ? (int)e : g_last_hip;
-  int rc = read_status(f->last_ctr_block, f->last_set_words, out);
+  int rc = read_status(f->last_ctr_block, f->last_set_words, f->info.n_cu, out);
   if (rc) return rc;
   if (e != hipSuccess) out->code = FLEET_EHIP;
   out->n_xcd = f->info.n_xcd;
@@ -884,7 +946,7 @@ int fleet_gemm(int32_t B, int32_t K, int32_t N, const void* x, const void* const
   }
   fleet_status_t status;
   memset(&status, 0, sizeof(status));
-  const int src = he == hipSuccess ? read_status(ctr, set_words, &status) : FLEET_OK;
+  const int src = he == hipSuccess ? read_status(ctr, set_words, info.n_cu, &status) : FLEET_OK;
   if (e0) (void)hipEventDestroy(e0);
   if (e1) (void)hipEventDestroy(e1);
   free_all();
