@@ -320,6 +320,12 @@ int fleet_last_status(fleet_t *f, fleet_status_t *out);
 int fleet_test_counter(fleet_t *f, int32_t static_block, int32_t set, int32_t word, uint32_t value);
 
 /*
+ * fleet_test_expect_workers (test): the workers per XCD that the handle's next steps expect (HOST array of 8, their
+ * sum the device's CU count) instead of those that fleet_create saw.  A hint: steps are right whatever it says.
+ */
+int fleet_test_expect_workers(fleet_t *f, const int32_t *per_xcd);
+
+/*
  * fleet_device_probe: XCD id (hardware XCC_ID) of each of n_blocks workgroups of
  * a grid launched the way the persistent kernel is; xcd_of_block is a HOST array
  * of n_blocks int32.  Paper section 4.1 (workers discover their XCD).

@@ -29,6 +29,7 @@ EXPORTS = (
     "fleet_device_probe", "fleet_copy", "fleet_weight_bytes", "fleet_weight_bytes_per_xcd",
     "fleet_l2_window_bytes", "fleet_l2_hit_model", "fleet_effective_intensity",
     "fleet_step_bytes", "fleet_strerror", "fleet_test_counter",
+    "fleet_test_expect_workers",
 )
 
 
@@ -254,6 +255,12 @@ def fleet_test_counter(f: Fleet, static_block: bool, which_set: int, word: int, 
                                            C.c_uint32(value))
     if rc != 0:
         raise FleetError(rc, "fleet_test_counter")
+
+
+def fleet_test_expect_workers(f: Fleet, per_xcd) -> None:
+    rc = load_library().fleet_test_expect_workers(f.handle, (C.c_int32 * 8)(*per_xcd))
+    if rc != 0:
+        raise FleetError(rc, "fleet_test_expect_workers")
 
 
 def fleet_copy(dst, src, nbytes: int, stream=0) -> None:

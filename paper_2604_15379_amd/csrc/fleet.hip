@@ -825,6 +825,18 @@ int fleet_test_counter(fleet_t* f, int32_t static_block, int32_t set, int32_t wo
   return FLEET_OK;
 }
 
+int fleet_test_expect_workers(fleet_t* f, const int32_t* per_xcd) {
+  if (!f || !per_xcd) return FLEET_EINVAL;
+  int sum = 0;
+  for (int x = 0; x < dev::MAX_XCD; ++x) {
+    if (per_xcd[x] < 0 || (per_xcd[x] > 0 && x >= f->info.n_xcd)) return FLEET_EINVAL;
+    sum += per_xcd[x];
+  }
+  if (sum != f->info.n_cu) return FLEET_EINVAL;   // (start-up relies on it)
+  memcpy(f->info.per_xcd, per_xcd, sizeof(f->info.per_xcd));
+  return FLEET_OK;
+}
+
 int fleet_last_status(fleet_t* f, fleet_status_t* out) {
   if (!f || !out) return FLEET_EINVAL;
   memset(out, 0, sizeof(*out));

@@ -105,3 +105,22 @@ def test_replays_of_a_captured_step_are_right_after_any_leftovers(steps):
         code = F.fleet_last_status(steps.f)["code"]
         _same((code, steps.hout, steps.logits), ref)
         _same(steps.run(torch.cuda.default_stream()), ref)      # eager steps in between
+
+
+@pytest.mark.parametrize("expect", [[33, 31] + [32] * 6, [0, 64] + [32] * 6, [256] + [0] * 7, [1, 63, 16, 48, 30, 34, 32, 32]],
+                         ids=lambda e: "-".join(map(str, e)))
+def test_steps_do_not_depend_on_the_expected_workers(steps, expect):
+    """Start-up is told how many workers to expect on each XCD; where that is wrong it adds up the rosters instead."""
+    default = torch.cuda.default_stream()
+    ref = steps.run(default)
+    status = F.fleet_last_status(steps.f)
+    if status["workers"] != [32] * 8:
+        pytest.skip(f"the numbers are for 32 workers on each of eight XCDs, not {status['workers']}")
+    print(f"expected workers {expect}", flush=True)
+    F.fleet_test_expect_workers(steps.f, expect)
+    for _ in range(3):
+        _same(steps.run(default), ref)
+        assert F.fleet_last_status(steps.f)["workers"] == status["workers"]
+    for bad in ([32] * 7 + [31], [-1, 65] + [32] * 6):
+        with pytest.raises(F.FleetError):
+            F.fleet_test_expect_workers(steps.f, bad)
