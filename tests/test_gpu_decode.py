@@ -252,6 +252,39 @@ def test_plan_is_kept_over_the_steps_of_a_launch():
     assert_close(res[0][1], res[1][1], "hidden_out of the last step")
 
 
+@pytest.mark.parametrize("batch,max_batch", [(3, 3), (20, 32), (40, 64), (100, 128)])
+def test_greedy_steps_have_the_same_bits_in_one_launch_and_in_many(batch, max_batch):
+    """Unequal lengths at the edges of 64-key units, so that plans change from step to step: the steps of one launch, one launch
+    per step, and fleet_decode_step with the tokens chosen outside give the same bits."""
+    n_tokens = 5
+    sh = si.Shape(2, 1024, 8, 8, 128, 1024, 1024, max_batch, 720)
+    pos = np.random.default_rng(batch).choice([20, 126, 190, 191, 254, 382, 446, 574, 638, 710], batch).astype(np.int32)
+    m = Model(sh, seed=92, batch=batch, positions=pos, with_embed=True)
+    f = F.fleet_create(sh.asdict(), m.w, 0, 0, 0)
+    res = []
+    try:
+        for per_launch in (n_tokens, 1, 0):
+            print(f"batch {batch}: {n_tokens} tokens, {per_launch} per launch", flush=True)
+            kc, vc, cur = m.kc.clone(), m.vc.clone(), m.pos.clone()
+            tok = torch.arange(batch, device="cuda", dtype=torch.int32) * 7
+            hout, logits = torch.zeros((batch, sh.hidden), device="cuda"), torch.zeros((batch, sh.vocab), device="cuda")
+            for _ in range(n_tokens // max(1, per_launch)):
+                if per_launch:
+                    out = torch.empty((per_launch, batch), device="cuda", dtype=torch.int32)
+                    F.fleet_decode_tokens(f, batch, tok, kc, vc, cur, per_launch, out, hout, logits)
+                else:
+                    F.fleet_decode_step(f, batch, None, tok, kc, vc, cur, hout, logits)
+                    tok = logits.argmax(1).to(torch.int32)
+                    cur = cur + 1
+                assert F.fleet_last_status(f)["code"] == 0
+            res.append((tok, cur, hout, logits, kc, vc))
+    finally:
+        F.fleet_destroy(f)
+    for other in res[1:]:
+        for got, ref in zip(other, res[0]):
+            assert torch.equal(got, ref)
+
+
 @pytest.mark.parametrize("batch", [1, 3, 20, 40])
 def test_layer_range_on_a_callers_stream(batch):
     """fleet_decode_layers on a caller's fp32 rows, in place, out of place and from rows aligned to 4 bytes only,
