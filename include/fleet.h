@@ -313,6 +313,13 @@ int fleet_trace_read(fleet_t *f, void *buf, size_t *len);
 int fleet_last_status(fleet_t *f, fleet_status_t *out);
 
 /*
+ * fleet_last_plan (test / measurement): synchronise the device and store into form[0..7] (HOST) how the keys of each
+ * XCD's attention stage were dealt to its workers in the last step: 0 by the graph (one task per sequence, kv
+ * head and split), 1 whole workers per (sequence, kv head) pair, 2 the pairs end to end in equal pieces.
+ */
+int fleet_last_plan(fleet_t *f, int32_t *form);
+
+/*
  * fleet_test_counter (test): synchronise the device and store `value` in word `word` of the dependency
  * counters -- of the handle, or (static_block != 0) of the array of fleet_decode_step_static -- as a
  * step that another one disturbed may leave it.  set 0: the counters the next step works on; 1: the other ones.

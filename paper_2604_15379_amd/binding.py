@@ -28,7 +28,7 @@ EXPORTS = (
     "fleet_graph_build", "fleet_graph_dump", "fleet_trace_read", "fleet_last_status",
     "fleet_device_probe", "fleet_copy", "fleet_weight_bytes", "fleet_weight_bytes_per_xcd",
     "fleet_l2_window_bytes", "fleet_l2_hit_model", "fleet_effective_intensity",
-    "fleet_step_bytes", "fleet_strerror", "fleet_test_counter",
+    "fleet_step_bytes", "fleet_strerror", "fleet_last_plan", "fleet_test_counter",
     "fleet_test_expect_workers",
 )
 
@@ -255,6 +255,14 @@ def fleet_test_counter(f: Fleet, static_block: bool, which_set: int, word: int, 
                                            C.c_uint32(value))
     if rc != 0:
         raise FleetError(rc, "fleet_test_counter")
+
+
+def fleet_last_plan(f: Fleet) -> list:
+    form = (C.c_int32 * 8)()
+    rc = load_library().fleet_last_plan(f.handle, form)
+    if rc != 0:
+        raise FleetError(rc, "fleet_last_plan")
+    return list(form)
 
 
 def fleet_test_expect_workers(f: Fleet, per_xcd) -> None:

@@ -805,6 +805,16 @@ int fleet_decode_tokens(fleet_t* f, int32_t batch, int32_t* tokens, void* k_cach
   return run_layers(f, a, (hipStream_t)stream);
 }
 
+int fleet_last_plan(fleet_t* f, int32_t* form) {
+  if (!f || !form) return FLEET_EINVAL;
+  HIP_TRY(hipDeviceSynchronize());
+  uint32_t set = 0, w[dev::C_READY];
+  HIP_TRY(hipMemcpy(&set, f->last_ctr_block, sizeof(set), hipMemcpyDeviceToHost));
+  HIP_TRY(hipMemcpy(w, f->last_ctr_block + dev::CTR_HEAD + (size_t)((set & 1) ^ 1) * f->last_set_words, sizeof(w), hipMemcpyDeviceToHost));
+  for (int x = 0; x < dev::MAX_XCD; ++x) form[x] = (int32_t)w[dev::C_ROSTER + 32 * x + dev::C_PLAN];
+  return FLEET_OK;
+}
+
 int fleet_test_counter(fleet_t* f, int32_t static_block, int32_t set, int32_t word, uint32_t value) {
   if (!f || set < 0 || set > 1 || word < 0) return FLEET_EINVAL;
   uint32_t* block = (uint32_t*)f->work;

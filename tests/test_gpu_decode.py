@@ -222,8 +222,144 @@ def test_attention_by_plan_of_unequal_lengths(nq, nkv, batch, tile_m, sched):
     assert_close(hout.cpu().numpy(), ho[:n], "hidden_out, paged")
 
 
+def _pools(kc, vc, n, page, table):
+    """The caches of the first n sequences as page pools laid out by ``table``."""
+    out = []
+    for src in (kc, vc):
+        dst = torch.zeros((src.shape[0], int(table.max()) + 1, src.shape[2], page, 128), dtype=src.dtype, device="cuda")
+        for i in range(table.shape[1]):
+            part = src[:, :n, :, page * i:page * (i + 1)]
+            dst[:, table[:, i].long().cuda(), :, :part.shape[3]] = part
+        out.append(dst)
+    return out
+
+
+class _PlanCase:
+    """A handle for more sequences than the step has, and steps through the entry points on unequal lengths."""
+
+    def __init__(self, batch, max_batch, nkv, sched=0, tile_m=0, equal=False, seed=1):
+        self.sh = si.Shape(1, 512, 2 * nkv, nkv, 128, 512, 0, max_batch, 700)
+        pos = np.full(batch, 333, np.int32) if equal else _plan_lengths(batch, batch + nkv)
+        self.m = Model(self.sh, seed=seed, batch=batch, positions=pos)
+        self.f = F.fleet_create(self.sh.asdict(), self.m.w, sched, tile_m, 0)
+        self.per = 11
+        self.table = torch.randperm(self.per * batch, generator=torch.Generator().manual_seed(batch)).to(torch.int32).view(batch, self.per)
+
+    def __enter__(self):
+        return self
+
+    def __exit__(self, *exc):
+        F.fleet_destroy(self.f)
+
+    def step(self, entry="step", pos=None, table=None, kc=None, vc=None):
+        """(status code, hidden_out, caches) of one step"""
+        m, n = self.m, self.m.batch
+        pos = m.pos if pos is None else torch.tensor(pos, device="cuda")
+        kc, vc = (m.kc if kc is None else kc).clone(), (m.vc if vc is None else vc).clone()
+        hout = torch.full((n, self.sh.hidden), float("nan"), device="cuda", dtype=torch.float32)
+        if entry == "paged":
+            kc, vc = _pools(kc, vc, n, 64, self.table)
+            table = (self.table if table is None else table).contiguous().cuda()
+            F.fleet_decode_step_paged(self.f, n, m.hidden, None, kc, vc, table, 64, self.table.numel(), self.per, pos, hout, None)
+        else:
+            call = F.fleet_decode_step_static if entry == "static" else F.fleet_decode_step
+            call(self.f, n, m.hidden, None, kc, vc, pos, hout, None)
+        return F.fleet_last_status(self.f)["code"], hout, kc, vc
+
+
+WHOLE, END_TO_END = 1, 2
+
+
+@pytest.mark.parametrize("batch,max_batch,nkv,sched,tile_m,equal,form", [
+    (17, 32, 8, 0, 0, False, WHOLE), (20, 32, 8, 0, 0, False, WHOLE), (20, 32, 8, 2, 0, False, WHOLE), (30, 64, 8, 0, 32, False, WHOLE),
+    (33, 64, 8, 0, 0, False, END_TO_END), (64, 64, 8, 0, 0, False, END_TO_END), (128, 128, 8, 0, 0, False, END_TO_END), (64, 64, 8, 2, 32, False, END_TO_END),
+    (32, 32, 8, 0, 0, True, 0), (64, 64, 8, 0, 0, True, 0), (128, 128, 8, 0, 0, True, 0),        # equal lengths
+    (16, 16, 8, 0, 0, False, 0), (33, 64, 8, 0, 16, False, 0), (33, 64, 8, 1, 0, False, 0)])     # 16-row tiles, chiplet-unaware schedule
+def test_which_steps_run_by_plan(batch, max_batch, nkv, sched, tile_m, equal, form):
+    """Unequal lengths at 32- and 64-row tiles: whole workers per pair where an XCD has more workers than pairs, the pairs
+    end to end where it has fewer; on every entry point, with the same bits in the static workspace."""
+    with _PlanCase(batch, max_batch, nkv, sched, tile_m, equal) as c:
+        ref = None
+        for entry in ("step", "paged", "static"):
+            print(f"plan of batch {batch}/{max_batch} nkv {nkv} sched {sched} tile_m {tile_m} equal {equal}: {entry}", flush=True)
+            code, hout, kc, vc = c.step(entry)
+            assert code == 0
+            assert F.fleet_last_plan(c.f) == [form] * 8
+            if entry == "step":
+                ref = (hout, kc, vc)
+                (ho, _), _, _ = c.m.run_oracle()
+            elif entry == "static":
+                assert all(torch.equal(a, b) for a, b in zip((hout, kc, vc), ref))
+            assert_close(hout.cpu().numpy(), ho, "hidden_out")
+
+
+@pytest.mark.parametrize("batch,max_batch,form", [(20, 32, WHOLE), (64, 64, END_TO_END)])
+def test_bad_positions_and_pages_under_a_plan(batch, max_batch, form):
+    """A position outside the cache, a page outside the pool and a table that is too short end a step that runs by plan as they end any
+    other (also where the piece is not its worker's first and other pieces have partial results pending): reported, nothing
+    written but the new slots of the other sequences, and the next step is right."""
+    with _PlanCase(batch, max_batch, 8) as c:
+        good = {e: c.step(e) for e in ("step", "paged")}
+        assert good["step"][0] == 0 and good["paged"][0] == 0
+        pos0 = c.m.pos_host
+        for row in sorted({0, 1, 5, batch // 3, batch // 2, batch - 1}):
+            for kind in ("position -1", "position max_seq", "page -1", "page n_pages"):
+                print(f"batch {batch} row {row}: {kind}", flush=True)
+                pos, table = pos0.copy(), c.table.clone()
+                entry = "paged" if kind.startswith("page") else "step"
+                if entry == "step":
+                    pos[row] = -1 if kind.endswith("-1") else c.sh.max_seq
+                else:
+                    table[row, pos0[row] // 64] = -1 if kind.endswith("-1") else c.table.numel()
+                code, _, kc, vc = c.step(entry, pos, table)
+                assert code == -1
+                assert F.fleet_last_plan(c.f) == [form] * 8
+                if entry == "step":
+                    for got, before in ((kc, c.m.kc), (vc, c.m.vc)):
+                        new = torch.zeros(got.shape[1], got.shape[3], dtype=torch.bool, device="cuda")
+                        for b in range(batch):
+                            if b != row:
+                                new[b, int(pos0[b])] = True
+                        diff = (got.view(torch.int16) != before.view(torch.int16)).any(-1).any(2).any(0)
+                        assert not (diff & ~new).any()
+                got = c.step(entry)
+                assert got[0] == 0 and torch.equal(got[1], good[entry][1])
+
+
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("batch,max_batch", [(1, 1), (3, 3), (20, 32), (64, 64)])
+def test_infinities_and_nans_in_the_cache_stay_with_their_sequence(batch, max_batch, paged):
+    """Slots beyond a sequence's length may hold anything.  A value or key that is not finite inside it makes that sequence's row not a
+    number throughout (the output projection adds every attention output to every feature, and the norm divides by the row's
+    size), and leaves every bit of the other rows as it was."""
+    entry = "paged" if paged else "step"
+    with _PlanCase(max(batch, 6), max_batch, 8) if batch > 3 else _PlanCase(batch, max_batch, 8, equal=True) as c:
+        code, ref, _, _ = c.step(entry)
+        assert code == 0 and torch.isfinite(ref).all()
+        beyond = torch.arange(700, device="cuda")[None, :] >= c.m.pos[:, None]          # [batch][slot]
+        for bad in (float("nan"), float("inf")):
+            print(f"batch {batch} paged {paged}: {bad} beyond the lengths", flush=True)
+            kc, vc = c.m.kc.clone(), c.m.vc.clone()
+            for t in (kc, vc):
+                t[:, :batch].masked_fill_(beyond[None, :, None, :, None], bad)
+            code, got, _, _ = c.step(entry, kc=kc, vc=vc)
+            assert code == 0 and torch.equal(got, ref)
+        row = int(c.m.pos.argmax())
+        others = [b for b in range(batch) if b != row]
+        for what in ("k", "v"):
+            for bad in (float("nan"), float("inf"), float("-inf")):
+                print(f"batch {batch} paged {paged}: {bad} in a {what} of sequence {row}", flush=True)
+                kc, vc = c.m.kc.clone(), c.m.vc.clone()
+                (kc if what == "k" else vc)[0, row, 2, 100, 37] = bad
+                code, got, _, _ = c.step(entry, kc=kc, vc=vc)
+                assert code == 0
+                assert torch.equal(got[others], ref[others])
+                if what == "v" or bad != bad:        # (a key's infinity may just have its weight vanish)
+                    assert torch.isnan(got[row]).all()
+
+
 def test_plan_is_kept_over_the_steps_of_a_launch():
-    """One launch of 70 greedy steps (a plan serves 64) equals 70 launches of one: a head whose row t + 1 is the
+    """One launch of 70 greedy steps (working by plan throughout, a new one for every step) equals 70 launches of one: a head whose row t + 1 is the
     embedding's row t makes the next token certain, the last hidden states agree to the parity bar."""
     batch, n_tokens = 20, 70
     sh = si.reduced_shape(max_batch=batch, max_seq=900, n_layers=1, vocab=1024)
