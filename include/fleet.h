@@ -166,7 +166,7 @@ int fleet_create(const fleet_shape_t *shape, const fleet_weights_t *weights, fle
  *              the step); not advanced by the library
  *   hidden_out device fp32 [batch, hidden]: residual stream after the last layer
  *   logits     device fp32 [batch, vocab], or NULL: the step then ends after the last
- *              layer and the final norm (no LM head)
+ *              layer (no final norm, no LM head)
  * hidden_in, the caches, hidden_out and logits must be 16-byte aligned (FLEET_EINVAL
  * otherwise): the kernels move them in 16-byte pieces.
  * The call launches one kernel on `stream` and does nothing else: no allocation, no
@@ -178,7 +178,10 @@ int fleet_create(const fleet_shape_t *shape, const fleet_weights_t *weights, fle
  * fleet_last_status() reports FLEET_ETIMEOUT.
  * The result is a function of the inputs alone: every reduction has a fixed order, so
  * repeating the step on the same inputs gives the same bits (for a given batch size,
- * schedule and tile height).
+ * schedule and tile height).  The positions are inputs too: with 32- and 64-row tiles (from 17
+ * sequences on) the XCD-aware schedules deal the keys of the step to the workers by the lengths of
+ * all its sequences, so the order in which one sequence's keys are added up, and with it the last
+ * bits of its row, may change with the lengths of the others.
  */
 int fleet_decode_step(fleet_t *f, int32_t batch, const void *hidden_in, const int32_t *tokens,
                       void *k_cache, void *v_cache, const int32_t *positions,
@@ -202,12 +205,14 @@ int fleet_destroy(fleet_t *f);
  * fleet_decode_step_static: fleet_decode_step for callers that cannot allocate device
  * memory and want none held per fleet_t for the step's working set (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc).  The working memory of the
- * step -- activations, split-KV and split-K partial sums, dependency counters, status block
- * -- lives in a static device array of FLEET_STATIC_SCRATCH_BYTES that the library's code
- * object carries (every GPU the library runs on holds it until the process ends) instead
- * of the fleet's own allocation.  Arguments and results as fleet_decode_step; the results
- * are bit-identical to it.  A step whose working memory exceeds the array (large batches on
- * the MFMA path with split-K partial sums; the Qwen3-8B shape fits up to batch 16) is
+ * step -- activations, split-KV and split-K partial sums, dependency counters -- lives in a
+ * static device array that the library's code object carries (every GPU the library runs on
+ * holds it until the process ends) instead of the fleet's own allocation: the counters, then
+ * FLEET_STATIC_SCRATCH_BYTES, then the pieces of attention that runs by the lengths (counters
+ * and pieces: 1.8 MB more).  Arguments and results as fleet_decode_step; the results
+ * are bit-identical to it.  A step whose working memory exceeds FLEET_STATIC_SCRATCH_BYTES (large
+ * batches on the MFMA path with split-K partial sums; the Qwen3-8B shape fits up to batch 16; one set
+ * of counters and 256 bytes are reckoned in, so that what is refused does not depend on where they lie) is
  * refused with FLEET_ETOOBIG before anything is launched.  The call itself allocates
  * nothing, frees nothing and copies nothing from the host; the counters are cleared as for
  * fleet_decode_step (by the launch before, or by a kernel in front once the array has been used on
@@ -241,7 +246,7 @@ int fleet_decode_step_paged(fleet_t *f, int32_t batch, const void *hidden_in, co
  * fleet_decode_tokens: n_tokens greedy decode steps in ONE launch of the persistent kernel
  * (paper section 4.1: the kernel stays resident over the generated tokens; no return to the
  * host between steps).  Each step gathers embed[tokens[b]], runs the decoder stack and the LM
- * head as fleet_decode_step does, and a last stage of CU-tasks takes, per sequence, the index
+ * head as fleet_decode_step does (the same bits, however the steps are grouped into launches), and a last stage of CU-tasks takes, per sequence, the index
  * of the largest logit (the lowest index among equal ones) as the next token.
  *   tokens     device int32 [batch], in/out: the input token of the first step; on return
  *              the last token generated

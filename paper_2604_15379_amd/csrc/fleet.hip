@@ -317,7 +317,8 @@ void own_work(const fleet* f, const DevGraph* dg, Work* w) {
   w->ctr_set_words = f->ctr_set_words;
 }
 // What a step of graph dg counts against FLEET_STATIC_SCRATCH_BYTES: its working memory, one set of
-// counters with a head of 96 words, and 256 bytes of status.
+// counters with a head of 96 words, and 256 bytes more.  (The counters lie in front of those bytes; they are reckoned in so
+// that the same steps are accepted and refused as when they lay inside.)
 size_t static_need(const fleet* f, const DevGraph* dg) {
   return work_layout(f, dg, nullptr, nullptr) + align_up(((size_t)dg->ctr_words - dev::C_EVENTS + 96) * 4) + 256;
 }
