@@ -27,23 +27,23 @@ HBM_PEAK_GBPS = 8000.0
 # same counters read for a plain copy of known size.  Key: (batch, kv, kv_min, sched, tile_m, flags)
 # at 36 layers and seed 2; any other workload reports null unless --traffic-bytes is given.
 MEASURED_TRAFFIC = {
-    (1, 1024, 0, 0, 0, 0): 15450548864,
-    (1, 1024, 0, 1, 0, 0): 15431806304,
-    (1, 1024, 0, 0, 0, 64): 16205908416,
-    (1, 1024, 0, 0, 0, 256): 16262395008,
-    (8, 2048, 1024, 0, 0, 0): 17331194048,
-    (8, 2048, 1024, 0, 0, 4): 17343882048,
-    (8, 2048, 1024, 1, 0, 0): 17487087456,
-    (32, 2048, 1024, 0, 0, 0): 23608298240,
-    (32, 2048, 1024, 0, 16, 0): 24150736448,
-    (32, 2048, 1024, 1, 16, 0): 32720066496,
-    (32, 2048, 1024, 2, 16, 0): 38613665792,
-    (64, 4096, 0, 0, 0, 0): 55967937472,
-    (64, 4096, 0, 0, 16, 0): 57076790528,
-    (64, 4096, 0, 1, 16, 0): 81750251392,
-    (64, 4096, 0, 2, 16, 0): 100455350080,
-    (64, 4096, 0, 0, 16, 32): 56763077056,
-    (64, 4096, 0, 0, 16, 2048): 57070389632,
+    (1, 1024, 0, 0, 0, 0): 15422163616,
+    (1, 1024, 0, 1, 0, 0): 15414246272,
+    (1, 1024, 0, 0, 0, 64): 16196907856,
+    (1, 1024, 0, 0, 0, 256): 16248064144,
+    (8, 2048, 1024, 0, 0, 0): 17325551872,
+    (8, 2048, 1024, 0, 0, 4): 17343859520,
+    (8, 2048, 1024, 1, 0, 0): 17483153184,
+    (32, 2048, 1024, 0, 0, 0): 23610664256,
+    (32, 2048, 1024, 0, 16, 0): 24139679936,
+    (32, 2048, 1024, 1, 16, 0): 32707753984,
+    (32, 2048, 1024, 2, 16, 0): 38603898944,
+    (64, 4096, 0, 0, 0, 0): 55954839808,
+    (64, 4096, 0, 0, 16, 0): 57061564928,
+    (64, 4096, 0, 1, 16, 0): 81736576064,
+    (64, 4096, 0, 2, 16, 0): 100458856000,
+    (64, 4096, 0, 0, 16, 32): 56751606528,
+    (64, 4096, 0, 0, 16, 2048): 57065017984,
 }
 
 
