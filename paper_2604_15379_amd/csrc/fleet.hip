@@ -11,6 +11,7 @@
 #include <memory>
 #include <mutex>
 #include <new>
+#include <set>
 #include <vector>
 
 #include "../../include/fleet.h"
@@ -448,6 +449,20 @@ int upload_graph(DevGraph* dg, const fleet* f, const void* const* gemm_copies, i
         fat[(size_t)t * dev::FAT_WORDS + dev::FAT_GROUP] = e[Q_COUNT];
         fat[(size_t)t * dev::FAT_WORDS + dev::FAT_POS] = t - e[Q_FIRST];
       }
+    }
+  // O and down projections: the rows they add to are complete when the stage in front of theirs starts.  The workers of an XCD
+  // know that they are if they run a task of that stage (a model with few FFN units gives some XCDs none of gate/up: their
+  // workers come to the down projection straight from O, whose other XCDs may still be writing)
+  auto stage_key = [&](int xcd, int layer, int wkind) { return ((int64_t)xcd * (MAX_LAYERS + 1) + layer) * 32 + wkind; };
+  std::set<int64_t> runs;
+  auto op_of = [&](int t) { return &g.ops[(size_t)g.tasks[(size_t)t * TASK_WORDS + T_OP] * OP_WORDS]; };
+  for (int pass = 0; pass < 2; ++pass)
+    for (int t = 0; t < g.n_tasks(); ++t) {
+      const int32_t *tw = &g.tasks[(size_t)t * TASK_WORDS], *op = op_of(t);
+      if (tw[T_SCOPE] != S_CHIPLET || op[O_BODY] != B_GEMM) continue;
+      if (pass == 0) runs.insert(stage_key(tw[T_XCD], op[O_LAYER], op[O_WKIND]));
+      else if (op[O_WKIND] == W_O || op[O_WKIND] == W_DOWN)
+        fat[(size_t)t * dev::FAT_WORDS + dev::FAT_EARLY] = (int32_t)runs.count(stage_key(tw[T_XCD], op[O_LAYER], op[O_WKIND] == W_O ? W_QKV : W_GU));
     }
   if ((rc = upload(&dg->fat, fat.data(), fat.size() * 4))) return rc;
   // counter block: G[e], L[x][e], one arrival counter per (sequence, kv head) for the split-KV

@@ -479,6 +479,25 @@ def test_input_rows_from_token_ids_and_hidden_states(batch, hidden):
         assert step(0, None, tok, True)[0] == -1
 
 
+@pytest.mark.parametrize("ffn", [32, 64, 96, 128])
+@pytest.mark.parametrize("batch,fma_max", [(1, 1), (2, 8), (7, 8), (2, 1), (16, 1), (20, 1), (40, 1)])
+def test_ffn_with_fewer_units_than_xcds(monkeypatch, batch, fma_max, ffn):
+    """Where gate/up has no units for some XCDs, their workers come to the down projection straight from O: the rows it adds to
+    may only be read once gate/up has ended.  (Once read before the wait: stale rows, errors of 0.2 to 3 x RMS.)"""
+    monkeypatch.setenv("FLEET_FMA_MAX_BATCH", str(fma_max))
+    sh = si.Shape(2, 1024, 9, 3, 128, ffn, 0, batch, 200)
+    m = Model(sh, seed=131, batch=batch, positions=np.random.default_rng(batch).integers(0, 200, batch).astype(np.int32))
+    (ho, _), _, _ = m.run_oracle()
+    for sched in (0, 2):
+        print(f"ffn {ffn} batch {batch} fma_max {fma_max} sched {sched}", flush=True)
+        f = F.fleet_create(sh.asdict(), m.w, sched, 0, 0)
+        try:
+            for _ in range(5):
+                assert_close(m.run_gpu(fleet=f)[0], ho, "hidden_out")
+        finally:
+            F.fleet_destroy(f)
+
+
 @pytest.mark.parametrize("batch", [1, 2, 16, 20])
 @pytest.mark.parametrize("hidden", [4160, 8192])
 def test_hidden_sizes_above_4096(batch, hidden):
