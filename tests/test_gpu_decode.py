@@ -326,6 +326,31 @@ def test_bad_positions_and_pages_under_a_plan(batch, max_batch, form):
                 assert got[0] == 0 and torch.equal(got[1], good[entry][1])
 
 
+@pytest.mark.parametrize("batch,max_batch", [(3, 3), (20, 32), (64, 64)])
+def test_a_launch_that_runs_out_of_cache_slots_is_reported(batch, max_batch):
+    """A sequence that reaches the end of its cache in the third of five steps ends the launch; the next one is right."""
+    sh = si.Shape(1, 512, 16, 8, 128, 512, 512, max_batch, 700)
+    pos = np.minimum(_plan_lengths(max(batch, 6), 3)[:batch], 690).astype(np.int32)
+    m = Model(sh, seed=93, batch=batch, positions=pos, with_embed=True)
+    f = F.fleet_create(sh.asdict(), m.w, 0, 0, 0)
+    try:
+        res = []
+        for last in (None, 698, None):
+            print(f"batch {batch}: a sequence at {last}", flush=True)
+            kc, vc, cur = m.kc.clone(), m.vc.clone(), m.pos.clone()
+            if last is not None:
+                cur[batch // 2] = last
+            tok = torch.arange(batch, device="cuda", dtype=torch.int32)
+            out = torch.full((5, batch), -1, device="cuda", dtype=torch.int32)
+            hout, logits = torch.zeros((batch, sh.hidden), device="cuda"), torch.zeros((batch, sh.vocab), device="cuda")
+            F.fleet_decode_tokens(f, batch, tok, kc, vc, cur, 5, out, hout, logits)
+            assert F.fleet_last_status(f)["code"] == (0 if last is None else -1)
+            res.append((hout, out))
+        assert torch.equal(res[0][0], res[2][0]) and torch.equal(res[0][1], res[2][1])
+    finally:
+        F.fleet_destroy(f)
+
+
 @pytest.mark.parametrize("paged", [False, True])
 @pytest.mark.parametrize("batch,max_batch", [(1, 1), (3, 3), (20, 32), (64, 64)])
 def test_infinities_and_nans_in_the_cache_stay_with_their_sequence(batch, max_batch, paged):
