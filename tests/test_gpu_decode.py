@@ -293,6 +293,39 @@ def test_which_steps_run_by_plan(batch, max_batch, nkv, sched, tile_m, equal, fo
             assert_close(hout.cpu().numpy(), ho, "hidden_out")
 
 
+@pytest.mark.parametrize("batch,max_batch,nkv", [(28, 32, 8), (32, 32, 8), (64, 64, 4)])
+def test_pairs_laid_end_to_end_where_an_xcd_has_workers_to_spare(batch, max_batch, nkv):
+    """Lengths so unequal that whole workers per pair would leave one with a much longer piece than the others: a few long
+    sequences among short ones run end to end although an XCD has no more pairs than workers; equal to the oracle, also
+    over a paged cache and with a trace (bit for bit).  A long pair then spans several workers and ends inside one."""
+    sh = si.Shape(1, 512, 2 * nkv, nkv, 128, 512, 0, max_batch, 2500)
+    pos = np.full(batch, 70, np.int32)
+    pos[:4] = (2499, 64, 0, 127)
+    pos[5::6] = 2400 - 37 * np.arange(len(pos[5::6]))
+    pos[6::9] = 1000 + 64 * np.arange(len(pos[6::9]))
+    print(f"end to end: batch {batch}/{max_batch} nkv {nkv}", flush=True)
+    m = Model(sh, seed=77 + batch, batch=batch, positions=pos)
+    m.w["wo"][0].mul_(100.0)
+    m.w_host = si.weights_to_host(m.w)
+    (ho, _), k, v = m.run_oracle()
+    f = F.fleet_create(sh.asdict(), m.w, 0, 0, 0)
+    try:
+        got = m.run_gpu(fleet=f)
+        assert F.fleet_last_plan(f) == [END_TO_END] * 8
+        assert_close(got[0], ho, "hidden_out")
+        check_new_kv(m, got[2], got[3], k, v)
+        table = torch.randperm(40 * batch, generator=torch.Generator().manual_seed(batch)).to(torch.int32).view(batch, 40)
+        kc, vc = _pools(m.kc, m.vc, batch, 64, table)
+        hout = torch.full((batch, sh.hidden), float("nan"), device="cuda", dtype=torch.float32)
+        F.fleet_decode_step_paged(f, batch, m.hidden, None, kc, vc, table.cuda(), 64, 40 * batch, 40, m.pos, hout, None)
+        assert F.fleet_last_status(f)["code"] == 0
+        assert_close(hout.cpu().numpy(), ho, "hidden_out, paged")
+    finally:
+        F.fleet_destroy(f)
+    traced = m.run_gpu(0, 0, F.FLAG_TRACE)
+    assert np.array_equal(traced[0], got[0])
+
+
 @pytest.mark.parametrize("batch,max_batch,form", [(20, 32, WHOLE), (64, 64, END_TO_END)])
 def test_bad_positions_and_pages_under_a_plan(batch, max_batch, form):
     """A position outside the cache, a page outside the pool and a table that is too short end a step that runs by plan as they end any
