@@ -25,7 +25,7 @@
   extern template __global__ void fleet_persistent_kernel<V, false>(dev::Params);     \
   extern template __global__ void fleet_persistent_kernel<V, true>(dev::Params);
 FLEET_EXTERN_VARIANT(0) FLEET_EXTERN_VARIANT(1) FLEET_EXTERN_VARIANT(2) FLEET_EXTERN_VARIANT(3)
-FLEET_EXTERN_VARIANT(4) FLEET_EXTERN_VARIANT(5) FLEET_EXTERN_VARIANT(6)
+FLEET_EXTERN_VARIANT(4) FLEET_EXTERN_VARIANT(5) FLEET_EXTERN_VARIANT(6) FLEET_EXTERN_VARIANT(7)
 #undef FLEET_EXTERN_VARIANT
 
 // Workspace of fleet_decode_step_static, the entry point that allocates nothing: the
@@ -72,6 +72,7 @@ struct DevGraph {
   Graph g;
   int32_t *ops = nullptr, *tasks = nullptr, *events = nullptr, *qoff = nullptr, *qents = nullptr;
   int32_t* fat = nullptr;   // [n_tasks][FAT_WORDS]: task words, op words, weight pointers, id
+  bool wide = false;        // GEMMs in tiles of the whole batch of 65 .. 128 rows (wide_tiles)
   int ctr_words = 0, gcnt_base = 0;   // words of counters (a set), first of the split-K tile counters
   ~DevGraph() {
     for (void* p : {(void*)ops, (void*)tasks, (void*)events, (void*)qoff, (void*)qents, (void*)fat})
@@ -118,7 +119,8 @@ const void* kernel_variant(int v, bool paged = false) {
       case 3: return (const void*)fleet_persistent_kernel<3, true>;
       case 4: return (const void*)fleet_persistent_kernel<4, true>;
       case 5: return (const void*)fleet_persistent_kernel<5, true>;
-      default: return (const void*)fleet_persistent_kernel<6, true>;
+      case 6: return (const void*)fleet_persistent_kernel<6, true>;
+      default: return (const void*)fleet_persistent_kernel<7, true>;
     }
   }
   switch (v) {
@@ -128,17 +130,19 @@ const void* kernel_variant(int v, bool paged = false) {
     case 3: return (const void*)fleet_persistent_kernel<3>;
     case 4: return (const void*)fleet_persistent_kernel<4>;
     case 5: return (const void*)fleet_persistent_kernel<5>;
-    default: return (const void*)fleet_persistent_kernel<6>;
+    case 6: return (const void*)fleet_persistent_kernel<6>;
+    default: return (const void*)fleet_persistent_kernel<7>;
   }
 }
 // variant for a graph: FMA path by batch (1, 2, 4, 8), MFMA path by tile height
-int variant_for(int path, int batch, int tile_m) {
-  if (path == P_FMA) return batch <= 1 ? 0 : batch <= 2 ? 1 : batch <= 4 ? 2 : 3;
-  return tile_m <= 16 ? 4 : tile_m <= 32 ? 5 : 6;
+int variant_for(const DevGraph* dg) {
+  const int32_t* h = dg->g.header.data();
+  const int batch = h[H_BATCH], tile_m = h[H_TILE_M];
+  if (h[H_PATH] == P_FMA) return batch <= 1 ? 0 : batch <= 2 ? 1 : batch <= 4 ? 2 : 3;
+  return dg->wide ? dev::V_WHOLE : tile_m <= 16 ? 4 : tile_m <= 32 ? 5 : 6;
 }
 int launch_persistent(DevGraph* dg, dev::Params& P, int n_cu, hipStream_t st) {
-  const Graph& g = dg->g;
-  const int v = variant_for(g.header[H_PATH], g.header[H_BATCH], g.header[H_TILE_M]);
+  const int v = variant_for(dg);
   void* args[] = {(void*)&P};
   HIP_TRY(hipLaunchKernel(kernel_variant(v, P.page_size > 0), dim3(n_cu), dim3(dev::WG), args, LDS_BYTES, st));
   return FLEET_OK;
@@ -263,6 +267,18 @@ struct fleet {
 
 namespace {
 
+// bytes of one region of the graph's split-K partial sums: [k-slice][unit][m-tile][blocks x 256] fp32 of the largest operator
+size_t gpart_bytes(const Graph& g) {
+  size_t gp = 0;
+  for (int i = 0; i < g.n_ops(); ++i) {
+    const int32_t* o = &g.ops[(size_t)i * OP_WORDS];
+    if (o[O_BODY] != B_GEMM || o[O_PATH] != P_MFMA) continue;
+    const size_t ks = std::max(1, (o[O_AUX2] >> 16) & 15), nb = o[O_EPI] == E_SWIGLU_BF16 ? 2 : 1;
+    if (ks > 1) gp = std::max(gp, ks * nb * (size_t)o[O_N_UNITS] * o[O_M_TILES] * mfma_blocks(o[O_TILE_M]) * 256 * 4);
+  }
+  return align_up(gp);
+}
+
 // Working memory of one launch of graph dg besides the counter block, carved from `base` (may be
 // null: sizes only).  Returns the bytes needed.
 size_t work_layout(const fleet* f, const DevGraph* dg, char* base, Work* w) {
@@ -272,15 +288,7 @@ size_t work_layout(const fleet* f, const DevGraph* dg, char* base, Work* w) {
   const size_t NQKV = (size_t)(s.n_q_heads + 2 * s.n_kv_heads) * s.head_dim, QD = (size_t)s.n_q_heads * s.head_dim;
   const size_t grp = s.n_q_heads / s.n_kv_heads, S = std::max(1, g.header[H_N_SPLITS]);
   auto pad256 = [](size_t k) { return (k + 255) / 256 * 256; };
-  // partial sums of the graph's split-K operators: [k-slice][unit][m-tile][blocks x 256] fp32
-  size_t gp = 0;
-  for (int i = 0; i < g.n_ops(); ++i) {
-    const int32_t* o = &g.ops[(size_t)i * OP_WORDS];
-    if (o[O_BODY] != B_GEMM || o[O_PATH] != P_MFMA) continue;
-    const size_t ks = std::max(1, (o[O_AUX2] >> 16) & 15), nb = o[O_EPI] == E_SWIGLU_BF16 ? 2 : 1;
-    if (ks > 1) gp = std::max(gp, ks * nb * (size_t)o[O_N_UNITS] * o[O_M_TILES] * mfma_blocks(o[O_TILE_M]) * 256 * 4);
-  }
-  gp = align_up(gp);
+  const size_t gp = gpart_bytes(g);
   const size_t regions = s.sched_mode == FLEET_SCHED_UNAWARE ? 1 : dev::MAX_XCD;
   size_t off = 0;
   auto take = [&](size_t bytes) { char* p = base ? base + off : nullptr; off += align_up(bytes); return p; };
@@ -304,7 +312,7 @@ size_t work_layout(const fleet* f, const DevGraph* dg, char* base, Work* w) {
 // attention by plan: the kernels that can, under the XCD-aware schedules
 bool can_plan(const fleet* f, const DevGraph* dg) {
   const int32_t* h = dg->g.header.data();
-  return dev::variant_plans(variant_for(h[H_PATH], h[H_BATCH], h[H_TILE_M])) && f->shape.sched_mode != FLEET_SCHED_UNAWARE &&
+  return dev::variant_plans(variant_for(dg)) && f->shape.sched_mode != FLEET_SCHED_UNAWARE &&
          (h[H_BATCH] * f->shape.n_kv_heads + f->info.n_xcd - 1) / f->info.n_xcd <= dev::PLAN_PAIRS;
 }
 int ctr_set_words(const DevGraph* dg) { return (dg->ctr_words + 31) / 32 * 32; }
@@ -408,9 +416,39 @@ int resolve_weight(const fleet* f, int wkind, int layer, const void* const* gemm
   return FLEET_OK;
 }
 
-int upload_graph(DevGraph* dg, const fleet* f, const void* const* gemm_copies, int n_xcd) {
+// Batches of 65 to 128 rows under the cooperative schedule, where the caller leaves the tile height to the library: the graph
+// has two m-tiles of up to 64 rows per GEMM, and its chiplet-tasks are carried out in tiles of the whole batch
+// (gemm_tall_tile<8>).  Two m-tiles mean that every weight is taken in twice: one 8B layer at batch 100 / KV 100-1000 222 us that way,
+// 193 with whole tiles.  It takes weights that are worth it, 128 KB a worker: two layers of a model with hidden 1024 and FFN 3072 (48 KB) at batch 128
+// take 132 us with two m-tiles and 153 with whole tiles, whose split sums cost more than the weights.  An explicit height, the other schedules (whose tasks name an
+// m-tile) and the ablation without the streaming hint keep the 64-row tiles.
+bool wide_tiles(const Graph& g, int tile_m, int flags, int n_workers) {
+  if ((flags & FLEET_FLAG_NO_STREAM) || g.header[H_PATH] != P_MFMA || g.header[H_SCHED] != FLEET_SCHED_COOPERATIVE || tile_m != 0 || g.header[H_M_TILES] < 2) return false;
+  int64_t most = 0;
+  for (int i = 0; i < g.n_ops(); ++i) {
+    const int32_t* o = &g.ops[(size_t)i * OP_WORDS];
+    if (o[O_BODY] == B_GEMM && o[O_WKIND] != W_LM) most = std::max(most, (int64_t)o[O_K] * o[O_N] * (o[O_EPI] == E_SWIGLU_BF16 ? 4 : 2));
+  }
+  return most / n_workers >= 128 * 1024;
+}
+// an operator as its chiplet-tasks carry it out in whole-batch tiles: one m-tile, a plan of its own.  Its partial sums (a region per XCD,
+// only the XCD's own units) stay within part_bytes; where repetitions may overlap, k is only split if the graph's order counts on it.
+void widen_op(int32_t* o, int sched_flags, int n_xcd, int n_workers, size_t part_bytes, bool in_order) {
+  if (o[O_BODY] != B_GEMM) return;
+  const int nb = o[O_EPI] == E_SWIGLU_BF16 ? 2 : 1, mtb = (o[O_BATCH] + 15) / 16, ks = (o[O_AUX2] >> 16) & 15;
+  const bool split = !(sched_flags & FLEET_FLAG_NO_SPLITK) && o[O_N_UNITS] <= GEMM_TILE_COUNTERS && (in_order || ks > 1);
+  const MfmaPlan pl = plan_wide((o[O_N_UNITS] + n_xcd - 1) / n_xcd, n_workers / n_xcd, o[O_K], nb, mtb, split, (int64_t)nb * dev::variant_mt(dev::V_WHOLE), (int64_t)(part_bytes / 1024));
+  o[O_AUX2] = (o[O_AUX2] & ~((15 << 12) | (15 << 16) | (1 << 21))) | (pl.G << 12) | (pl.KS << 16);
+  o[O_M_TILES] = 1;
+  o[O_TILE_M] = 16 * dev::variant_mt(dev::V_WHOLE);
+}
+
+// (tile_m: as the caller asked for; part_bytes: one region of partial sums)
+int upload_graph(DevGraph* dg, const fleet* f, const void* const* gemm_copies, const DevInfo& info, int tile_m, int flags, size_t part_bytes) {
   const Graph& g = dg->g;
+  const int n_xcd = info.n_xcd;
   int rc;
+  dg->wide = wide_tiles(g, tile_m, flags, info.n_cu);
   if ((rc = upload(&dg->ops, g.ops.data(), g.ops.size() * 4))) return rc;
   if ((rc = upload(&dg->tasks, g.tasks.data(), g.tasks.size() * 4))) return rc;
   if ((rc = upload(&dg->events, g.events.data(), g.events.size() * 4))) return rc;
@@ -436,6 +474,7 @@ int upload_graph(DevGraph* dg, const fleet* f, const void* const* gemm_copies, i
     const int32_t* tw = &g.tasks[(size_t)t * TASK_WORDS];
     memcpy(d, tw, TASK_WORDS * 4);
     memcpy(d + TASK_WORDS, &g.ops[(size_t)tw[T_OP] * OP_WORDS], OP_WORDS * 4);
+    if (dg->wide) widen_op(d + TASK_WORDS, flags, n_xcd, info.n_cu, part_bytes, f != nullptr);
     memcpy(d + dev::FAT_W, &w[tw[T_OP]], sizeof(void*));
     memcpy(d + dev::FAT_W2, &w2[tw[T_OP]], sizeof(void*));
     d[dev::FAT_ID] = t;
@@ -596,7 +635,7 @@ int warm_kernels(fleet* f) {
   bool seen[dev::N_VARIANTS] = {false};
   for (auto& dgp : f->graphs) {
     DevGraph* dg = dgp.get();
-    const int v = variant_for(dg->g.header[H_PATH], dg->g.header[H_BATCH], dg->g.header[H_TILE_M]);
+    const int v = variant_for(dg);
     if (seen[v]) continue;
     seen[v] = true;
     Work w;
@@ -708,7 +747,7 @@ int fleet_create(const fleet_shape_t* shape, const fleet_weights_t* w, fleet_t**
       std::unique_ptr<DevGraph> dg(new (std::nothrow) DevGraph());
       if (!dg) return FLEET_ENOMEM;
       dg->g = build_decode_graph(f->shape, b, f->info.n_xcd, f->info.n_cu, loop != 0, f->fma_max);
-      if ((rc = upload_graph(dg.get(), f.get(), nullptr, f->info.n_xcd))) return rc;
+      if ((rc = upload_graph(dg.get(), f.get(), nullptr, f->info, shape->tile_m, shape->flags, gpart_bytes(dg->g)))) return rc;
       f->work_bytes = std::max(f->work_bytes, work_layout(f.get(), dg.get(), nullptr, nullptr));
       f->ctr_set_words = std::max(f->ctr_set_words, ctr_set_words(dg.get()));
       (loop ? f->graphs_loop : f->graphs).push_back(std::move(dg));
@@ -951,19 +990,19 @@ int fleet_gemm(int32_t B, int32_t K, int32_t N, const void* x, const void* const
     if ((rc = pack_matrix(&xp, x, B, K, false))) { free_all(); return rc; }
     if (hipDeviceSynchronize() != hipSuccess) { free_all(); return FLEET_EHIP; }
   }
-  if ((rc = upload_graph(&dg, nullptr, mfma ? (const void* const*)packed.data() : w_copies, info.n_xcd))) { free_all(); return rc; }
-  const int set_words = ctr_set_words(&dg);
-  if ((rc = upload(&ctr, nullptr, ctr_block_bytes(set_words)))) { free_all(); return rc; }
   // one region of partial sums: 8 k-slices of the batch padded to whole tiles; one region
   // per XCD under the XCD-aware schedules
-  const size_t gpart_bytes = (size_t)8 * ((B + MAX_TILE_ROWS - 1) / MAX_TILE_ROWS * MAX_TILE_ROWS) * N * 4;
-  if ((rc = upload(&gpart, nullptr, gpart_bytes * (sched_mode == FLEET_SCHED_UNAWARE ? 1 : dev::MAX_XCD)))) { free_all(); return rc; }
+  const size_t part_bytes = (size_t)8 * ((B + MAX_TILE_ROWS - 1) / MAX_TILE_ROWS * MAX_TILE_ROWS) * N * 4;
+  if ((rc = upload_graph(&dg, nullptr, mfma ? (const void* const*)packed.data() : w_copies, info, tile_m, flags, part_bytes))) { free_all(); return rc; }
+  const int set_words = ctr_set_words(&dg);
+  if ((rc = upload(&ctr, nullptr, ctr_block_bytes(set_words)))) { free_all(); return rc; }
+  if ((rc = upload(&gpart, nullptr, part_bytes * (sched_mode == FLEET_SCHED_UNAWARE ? 1 : dev::MAX_XCD)))) { free_all(); return rc; }
   dev::Params P;
   memset(&P, 0, sizeof(P));
   fill_graph_params(P, &dg, info);
   P.ctr_block = ctr; P.ctr_set_words = set_words;
   P.buf[BUF_GEMM_X] = mfma ? xp : (void*)x; P.buf[BUF_GEMM_Y] = y; P.buf[BUF_GPART] = gpart;
-  P.gpart_xcd_bytes = sched_mode == FLEET_SCHED_UNAWARE ? 0 : (int32_t)gpart_bytes;
+  P.gpart_xcd_bytes = sched_mode == FLEET_SCHED_UNAWARE ? 0 : (int32_t)part_bytes;
   P.n_iter = 1;
   P.timeout_ticks = timeout_ticks_from_env(); P.n_xcd = info.n_xcd; P.flags = flags;
   P.batch = B; P.hidden = K;

@@ -235,6 +235,28 @@ MfmaPlan plan_mfma(int ux, int wpx, int K, int nb, int mt_blocks, int m_tiles, b
   return best;
 }
 
+// A worker takes in 45 KB/us, weights and activations together (700 KB/us of weights per XCD at most); a tile costs 1.5 us on
+// top, a split-K tile 3.5 us and the last arriver's reading of all slices at 60 KB/us.
+MfmaPlan plan_wide(int ux, int wpx, int K, int nb, int mtb, bool allow_split, int64_t part_kb, int64_t max_part_kb) {
+  const int gmax = 6 / nb;
+  ux = std::max(1, ux); wpx = std::max(1, wpx);
+  MfmaPlan best{1, 1, 0};
+  int64_t best_cost = -1;
+  for (int G = 1; G <= std::min(gmax, ux); ++G)
+    for (int KS = 1; KS <= 8; KS *= 2) {
+      if (KS > 1 && (!allow_split || K % (KS * 128) != 0 || (int64_t)KS * ux * part_kb > max_part_kb)) continue;
+      const int64_t tiles = (int64_t)((ux + G - 1) / G) * KS, per_worker = (tiles + wpx - 1) / wpx, active = std::min<int64_t>(tiles, wpx);
+      const int64_t kc = K / KS, w_kb = G * nb * kc / 32, x_kb = mtb * kc / 32;
+      const int64_t stream = std::max((w_kb + x_kb) * 1000 / 45, w_kb * 1000 * active / 700);
+      int64_t cost = per_worker * (stream + (KS > 1 ? 3500 + (int64_t)KS * G * part_kb * 1000 / 60 : 1500));
+      if (tiles % wpx != 0) cost += cost / 10;
+      if (best_cost < 0 || cost < best_cost || (cost == best_cost && (G > best.G || (G == best.G && KS < best.KS)))) {
+        best_cost = cost; best.G = G; best.KS = KS;
+      }
+    }
+  return best;
+}
+
 // the plan of an operator with n_units units under the given schedule
 static MfmaPlan plan_for(int sched, int flags, int n_units, int K, int nb, int tile_m, int m_tiles, int n_xcd, int n_workers) {
   const bool split_ok = !(flags & FLEET_FLAG_NO_SPLITK) && (long)n_units * m_tiles <= GEMM_TILE_COUNTERS;

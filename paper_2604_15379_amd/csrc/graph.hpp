@@ -114,6 +114,9 @@ constexpr int GEMM_TILE_COUNTERS = 4096;
 constexpr int RESIDENT_UNITS = 2, RESIDENT_K = 4096;
 struct MfmaPlan { int G, KS, resident; };
 MfmaPlan plan_mfma(int units_per_xcd, int workers_per_xcd, int K, int nb, int mt_blocks, int m_tiles, bool allow_split);
+// the same for tiles of the whole batch of 65 .. 128 rows (mtb blocks of 16): units per tile and k-slices of an operator's
+// tiles, where one k-slice's partial sums are part_kb KB per unit and at most max_part_kb KB per XCD
+MfmaPlan plan_wide(int units_per_xcd, int workers_per_xcd, int K, int nb, int mtb, bool allow_split, int64_t part_kb, int64_t max_part_kb);
 // 16-row blocks of batch rows the MFMA kernel for tile height tile_m accumulates (1, 2 or 4)
 int mfma_blocks(int tile_m);
 // largest batch that runs the FMA GEMV kernels (larger batches run the MFMA kernels): 1, or

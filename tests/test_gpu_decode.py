@@ -919,3 +919,22 @@ def test_steps_after_an_aborted_one(static):
     finally:
         F.fleet_destroy(f)
         F.fleet_destroy(fresh)
+
+
+@pytest.mark.parametrize("batch", [65, 81, 128])
+def test_whole_batch_tiles_in_a_step(batch):
+    """65 to 128 sequences of a model whose weights are worth it run the GEMMs in tiles of the whole batch: equal to the oracle,
+    to a traced launch and to the static workspace bit for bit, and to 64-row tiles up to rounding; a handle made for more rows."""
+    sh = si.Shape(1, 2048, 16, 8, 128, 4096, 528, min(128, batch + 7), 200)
+    pos = np.random.default_rng(batch).integers(0, 200, batch).astype(np.int32)
+    m = Model(sh, seed=60 + batch, batch=batch, positions=pos)
+    (ho, lg), k, v = m.run_oracle()
+    print(f"whole batch {batch}", flush=True)
+    got = m.run_gpu()
+    assert_close(got[0], ho, "hidden_out")
+    assert_close(got[1], lg, "logits")
+    check_new_kv(m, got[2], got[3], k, v)
+    traced = m.run_gpu(0, 0, F.FLAG_TRACE)
+    assert np.array_equal(traced[0], got[0]) and np.array_equal(traced[1], got[1])
+    low = m.run_gpu(0, 64)
+    assert_close(low[0], got[0], "64-row tiles")

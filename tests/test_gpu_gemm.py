@@ -91,3 +91,13 @@ def test_fleet_copy_moves_bytes():
     F.fleet_copy(dst, src, src.numel() * 2, torch.cuda.current_stream().cuda_stream)
     torch.cuda.synchronize()
     assert torch.equal(src.view(torch.int16), dst.view(torch.int16))
+
+
+# more than 64 rows as one tile (weights of 128 KB a worker and more): one to eight blocks of rows beyond the tile's edge, units that do not divide
+# among the workers, k-slices, k-steps that end inside a round; reps = 3: counters of split tiles used again
+@pytest.mark.parametrize("B", [65, 80, 81, 112, 128])
+@pytest.mark.parametrize("K,N,reps", [(4096, 4096, 3), (4128, 4112, 1), (12288, 2048, 3), (1024, 20496, 1)])
+def test_gemm_whole_batch_tiles(B, K, N, reps):
+    print(f"gemm whole batch B={B} K={K} N={N}", flush=True)
+    y, ref, _ = _run(B, K, N, flags=F.FLAG_CHAINED if reps > 1 else 0, reps=reps, n_copies=min(reps, 2))
+    assert_close(y, ref, f"gemm B={B} K={K} N={N}", tol=1e-3)
