@@ -443,6 +443,30 @@ void widen_op(int32_t* o, int sched_flags, int n_xcd, int n_workers, size_t part
   o[O_TILE_M] = 16 * dev::variant_mt(dev::V_WHOLE);
 }
 
+// May an MFMA GEMM's chiplet-task invalidate the caches of its XCD before it waits for its input instead of afterwards (FAT_INV)?
+// Old lines of the input are in those caches because (1) the XCD's workers read the buffer's contents before, or (2) they wrote parts of a line, or wrote
+// all of it some time ago.  After the invalidate none may appear:
+// (1) the last stage that read the buffer is over when the worker gets here.  It comes from the chiplet-task before on its queue (stage
+//     prev_stage, or from the start of the launch), and that task's wait was for the stage in front of prev_stage: everything up to there is over.
+// (2) what the XCD still writes to the buffer are whole lines: a line of 128 bytes comes from one XCD.  True of the SwiGLU products (a line is 8 rows by 8 features, a
+//     unit's tile all of its 16 features), of the norm by operand blocks, of the attention output where a kv head's sequences share an XCD (8 rows by 8
+//     features of one head), and of the fp32 residual rows where every XCD's units of 64 bytes a row begin on a line.
+bool early_invalidate(const Graph& g, const int32_t* op, int stage, int prev_stage, int nkv, int flags, int n_xcd) {
+  const int in = op[O_IN_BUF];
+  if (op[O_PATH] != P_MFMA) return false;
+  for (int t = 0; t < g.n_tasks(); ++t) {
+    const int32_t *tw = &g.tasks[(size_t)t * TASK_WORDS], *o = &g.ops[(size_t)tw[T_OP] * OP_WORDS];
+    if (o[O_BODY] == B_GEMM && o[O_IN_BUF] == in && tw[T_STAGE] < stage && tw[T_STAGE] > prev_stage - 1) return false;
+  }
+  switch (in) {
+    case BUF_N: return dev::norm_by_blocks(op[O_K]);
+    case BUF_X: return op[O_K] % (32 * n_xcd) == 0;
+    case BUF_ATT: return nkv % n_xcd == 0;
+    case BUF_H: return !(flags & FLEET_FLAG_UNFUSED_SILU);
+    default: return false;
+  }
+}
+
 // (tile_m: as the caller asked for; part_bytes: one region of partial sums)
 int upload_graph(DevGraph* dg, const fleet* f, const void* const* gemm_copies, const DevInfo& info, int tile_m, int flags, size_t part_bytes) {
   const Graph& g = dg->g;
@@ -502,6 +526,18 @@ int upload_graph(DevGraph* dg, const fleet* f, const void* const* gemm_copies, c
       if (pass == 0) runs.insert(stage_key(tw[T_XCD], op[O_LAYER], op[O_WKIND]));
       else if (op[O_WKIND] == W_O || op[O_WKIND] == W_DOWN)
         fat[(size_t)t * dev::FAT_WORDS + dev::FAT_EARLY] = (int32_t)runs.count(stage_key(tw[T_XCD], op[O_LAYER], op[O_WKIND] == W_O ? W_QKV : W_GU));
+    }
+  if (f)
+    for (int x = 0; x < n_xcd; ++x) {
+      int prev_stage = 0;   // (no GEMM is in stage 0)
+      for (int qi = g.qoff[x]; qi < g.qoff[x + 1]; ++qi) {
+        const int32_t* e = &g.qents[(size_t)qi * QENT_WORDS];
+        if (e[Q_DIST] != D_CHIPLET) continue;
+        const int stage = g.tasks[(size_t)e[Q_FIRST] * TASK_WORDS + T_STAGE];
+        fat[(size_t)e[Q_FIRST] * dev::FAT_WORDS + dev::FAT_INV] =
+            early_invalidate(g, op_of(e[Q_FIRST]), stage, prev_stage, f->shape.n_kv_heads, flags, n_xcd) ? 1 : 0;
+        prev_stage = stage;
+      }
     }
   if ((rc = upload(&dg->fat, fat.data(), fat.size() * 4))) return rc;
   // counter block: G[e], L[x][e], one arrival counter per (sequence, kv head) for the split-KV

@@ -938,3 +938,36 @@ def test_whole_batch_tiles_in_a_step(batch):
     assert np.array_equal(traced[0], got[0]) and np.array_equal(traced[1], got[1])
     low = m.run_gpu(0, 64)
     assert_close(low[0], got[0], "64-row tiles")
+
+
+@pytest.mark.parametrize("sched", [0, 2])
+@pytest.mark.parametrize("batch,nkv,hidden,ffn", [(2, 8, 1024, 1024), (3, 2, 1088, 1024), (16, 8, 2048, 2048), (20, 8, 2048, 2048), (24, 2, 1024, 3072),
+                                                  (40, 8, 2048, 2048), (48, 4, 1056, 96), (100, 8, 2048, 4096)])
+def test_steps_on_changing_inputs_see_no_old_rows(batch, nkv, hidden, ffn, sched):
+    """Two sets of inputs in turn through one handle, three layers: every step has the bits of that set's first step.  A line of
+    activations of the step or the layer before, left in a cache that was invalidated too early, would show as a difference (hidden sizes at
+    which lines of the residual rows and of the norms do and do not come from one XCD, kv heads that share an XCD and that do not, few FFN units)."""
+    sh = si.Shape(3, hidden, 2 * nkv, nkv, 128, ffn, 528, batch, 150)
+    pos = np.random.default_rng(batch).integers(0, 150, batch).astype(np.int32)
+    m = Model(sh, seed=40 + batch, batch=batch, positions=pos)
+    f = F.fleet_create(sh.asdict(), m.w, sched, 16 if sched == 2 and batch > 16 else 0, 0)
+    sets = [(m.hidden, m.kc, m.vc), (m.hidden.flip(0).neg().contiguous(), m.kc.flip(3).contiguous(), m.vc.neg())]
+    stream = torch.cuda.current_stream().cuda_stream
+    ref = []
+    try:
+        for i in range(24):
+            x, kc, vc = sets[i % 2]
+            hout = torch.full((batch, hidden), float("nan"), device="cuda")
+            logits = torch.full((batch, sh.vocab), float("nan"), device="cuda")
+            F.fleet_decode_step(f, batch, x, None, kc.clone(), vc.clone(), m.pos, hout, logits, stream)
+            if i < 2:
+                ref.append((hout, logits))
+                assert torch.isfinite(hout).all() and torch.isfinite(logits).all()
+            else:
+                assert torch.equal(hout, ref[i % 2][0]) and torch.equal(logits, ref[i % 2][1]), f"step {i}"
+        assert F.fleet_last_status(f)["code"] == 0
+    finally:
+        F.fleet_destroy(f)
+    (ho, lg), _, _ = m.run_oracle()
+    assert_close(ref[0][0].cpu().numpy(), ho, "hidden_out")
+    assert_close(ref[0][1].cpu().numpy(), lg, "logits")
