@@ -451,13 +451,12 @@ void widen_op(int32_t* o, int sched_flags, int n_xcd, int n_workers, size_t part
 // (2) what the XCD still writes to the buffer are whole lines: a line of 128 bytes comes from one XCD.  True of the SwiGLU products (a line is 8 rows by 8 features, a
 //     unit's tile all of its 16 features), of the norm by operand blocks, of the attention output where a kv head's sequences share an XCD (8 rows by 8
 //     features of one head), and of the fp32 residual rows where every XCD's units of 64 bytes a row begin on a line.
-bool early_invalidate(const Graph& g, const int32_t* op, int stage, int prev_stage, int nkv, int flags, int n_xcd) {
+// (gemm_reads: (buffer, stage) of every GEMM task's input)
+bool early_invalidate(const std::set<std::pair<int, int>>& gemm_reads, const int32_t* op, int stage, int prev_stage, int nkv, int flags, int n_xcd) {
   const int in = op[O_IN_BUF];
   if (op[O_PATH] != P_MFMA) return false;
-  for (int t = 0; t < g.n_tasks(); ++t) {
-    const int32_t *tw = &g.tasks[(size_t)t * TASK_WORDS], *o = &g.ops[(size_t)tw[T_OP] * OP_WORDS];
-    if (o[O_BODY] == B_GEMM && o[O_IN_BUF] == in && tw[T_STAGE] < stage && tw[T_STAGE] > prev_stage - 1) return false;
-  }
+  const auto read = gemm_reads.lower_bound({in, prev_stage});
+  if (read != gemm_reads.end() && read->first == in && read->second < stage) return false;
   switch (in) {
     case BUF_N: return dev::norm_by_blocks(op[O_K]);
     case BUF_X: return op[O_K] % (32 * n_xcd) == 0;
@@ -538,8 +537,12 @@ int upload_graph(DevGraph* dg, const fleet* f, const void* const* gemm_copies, c
       if (tw[T_SCOPE] != S_CHIPLET || op[O_BODY] != B_GEMM) continue;
       if (pass == 0) runs.insert(stage_key(tw[T_XCD], op[O_LAYER], op[O_WKIND]));
       else if (op[O_WKIND] == W_O || op[O_WKIND] == W_DOWN)
-        fat[(size_t)t * dev::FAT_WORDS + dev::FAT_EARLY] = (int32_t)runs.count(stage_key(tw[T_XCD], op[O_LAYER], op[O_WKIND] == W_O ? W_QKV : W_GU));
+        fat[(size_t)t * dev::FAT_WORDS + dev::FAT_HINTS] = runs.count(stage_key(tw[T_XCD], op[O_LAYER], op[O_WKIND] == W_O ? W_QKV : W_GU)) ? dev::FAT_EARLY : 0;
     }
+  std::set<std::pair<int, int>> gemm_reads;
+  if (f)
+    for (int t = 0; t < g.n_tasks(); ++t)
+      if (op_of(t)[O_BODY] == B_GEMM) gemm_reads.insert({op_of(t)[O_IN_BUF], g.tasks[(size_t)t * TASK_WORDS + T_STAGE]});
   if (f)
     for (int x = 0; x < n_xcd; ++x) {
       int prev_stage = 0;   // (no GEMM is in stage 0)
@@ -547,8 +550,8 @@ int upload_graph(DevGraph* dg, const fleet* f, const void* const* gemm_copies, c
         const int32_t* e = &g.qents[(size_t)qi * QENT_WORDS];
         if (e[Q_DIST] != D_CHIPLET) continue;
         const int stage = g.tasks[(size_t)e[Q_FIRST] * TASK_WORDS + T_STAGE];
-        fat[(size_t)e[Q_FIRST] * dev::FAT_WORDS + dev::FAT_INV] =
-            early_invalidate(g, op_of(e[Q_FIRST]), stage, prev_stage, f->shape.n_kv_heads, flags, n_xcd) ? 1 : 0;
+        if (early_invalidate(gemm_reads, op_of(e[Q_FIRST]), stage, prev_stage, f->shape.n_kv_heads, flags, n_xcd))
+          fat[(size_t)e[Q_FIRST] * dev::FAT_WORDS + dev::FAT_HINTS] |= dev::FAT_INV;
         prev_stage = stage;
       }
     }
