@@ -301,6 +301,16 @@ int fleet_graph_build(const fleet_shape_t *shape, int32_t batch, int32_t n_xcd,
 int fleet_graph_dump(fleet_t *f, int32_t batch, void *buf, size_t *len);
 
 /*
+ * fleet_graph_build_run, fleet_graph_dump_run (test / measurement): the same graphs as the workers carry them out, in the
+ * same words: GEMM operators in tiles of the whole batch (65 to 128 rows: one m-tile, k-slices of their own),
+ * norm tasks on other ranks of their XCD, header word 16 the rows of the GEMM tiles that run (the builder's graph has 0
+ * there), task word 10 the hints to the task (csrc/graph.hpp).  Tasks, events, queues and stages are those of the graph.
+ */
+int fleet_graph_build_run(const fleet_shape_t *shape, int32_t batch, int32_t n_xcd,
+                          int32_t n_workers, void *buf, size_t *len);
+int fleet_graph_dump_run(fleet_t *f, int32_t batch, void *buf, size_t *len);
+
+/*
  * fleet_trace_read (needs FLEET_FLAG_TRACE or FLEET_FLAG_TIMING): copy the last
  * step's execution records to host memory after synchronising the device.  Each
  * record is 8 int32 words: task, worker (workgroup id), xcd, time the task was

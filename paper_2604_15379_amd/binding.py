@@ -29,7 +29,7 @@ EXPORTS = (
     "fleet_device_probe", "fleet_copy", "fleet_weight_bytes", "fleet_weight_bytes_per_xcd",
     "fleet_l2_window_bytes", "fleet_l2_hit_model", "fleet_effective_intensity",
     "fleet_step_bytes", "fleet_strerror", "fleet_last_plan", "fleet_test_counter",
-    "fleet_test_expect_workers",
+    "fleet_test_expect_workers", "fleet_graph_build_run", "fleet_graph_dump_run",
 )
 
 
@@ -227,6 +227,17 @@ def fleet_graph_dump(f: Fleet, batch: int) -> np.ndarray:
     return _sized_call(load_library().fleet_graph_dump, f.handle, C.c_int32(batch))
 
 
+def fleet_graph_build_run(shape: dict, batch: int, n_xcd: int = 8, n_workers: int = 256,
+                          sched_mode=0, tile_m=0, flags=0) -> np.ndarray:
+    sh = _shape_struct(shape, sched_mode, tile_m, flags)
+    return _sized_call(load_library().fleet_graph_build_run, C.byref(sh), C.c_int32(batch),
+                       C.c_int32(n_xcd), C.c_int32(n_workers))
+
+
+def fleet_graph_dump_run(f: Fleet, batch: int) -> np.ndarray:
+    return _sized_call(load_library().fleet_graph_dump_run, f.handle, C.c_int32(batch))
+
+
 def fleet_trace_read(f: Fleet) -> np.ndarray:
     """[n_records, 8] int32: task, worker, xcd, t_enter, ticket0, ticket1, t0, t1."""
     return _sized_call(load_library().fleet_trace_read, f.handle).reshape(-1, 8)
@@ -307,10 +318,10 @@ def fleet_step_bytes(shape: dict, batch: int, positions) -> int:
 # ---------------------------------------------------------------- graph words -> dict
 HEADER_WORDS, OP_WORDS, TASK_WORDS, EVENT_WORDS, QENT_WORDS = 32, 16, 16, 4, 4
 H_NAMES = ("magic", "version", "n_ops", "n_tasks", "n_events", "n_xcd", "n_qent", "n_layers",
-           "batch", "sched", "tile_m", "path", "n_splits", "n_workers", "m_tiles", "total_words")
+           "batch", "sched", "tile_m", "path", "n_splits", "n_workers", "m_tiles", "total_words", "run_tile_m")
 O_NAMES = ("body", "layer", "epi", "path", "K", "N", "unit_rows", "n_units", "m_tiles", "tile_m",
            "in_buf", "out_buf", "aux", "wkind", "batch", "aux2")
-T_NAMES = ("op", "scope", "xcd", "a0", "a1", "a2", "a3", "wait_event", "signal_event", "stage")
+T_NAMES = ("op", "scope", "xcd", "a0", "a1", "a2", "a3", "wait_event", "signal_event", "stage", "hints")
 
 
 def parse_graph(words: np.ndarray) -> dict:

@@ -11,7 +11,6 @@
 #include <memory>
 #include <mutex>
 #include <new>
-#include <set>
 #include <vector>
 
 #include "../../include/fleet.h"
@@ -69,10 +68,9 @@ struct Work {
 };
 
 struct DevGraph {
-  Graph g;
+  Graph g, run;             // as built, as carried out (run_graph)
   int32_t *ops = nullptr, *tasks = nullptr, *events = nullptr, *qoff = nullptr, *qents = nullptr;
   int32_t* fat = nullptr;   // [n_tasks][FAT_WORDS]: task words, op words, weight pointers, id
-  bool wide = false;        // GEMMs in tiles of the whole batch of 65 .. 128 rows (wide_tiles)
   int ctr_words = 0, gcnt_base = 0;   // words of counters (a set), first of the split-K tile counters
   ~DevGraph() {
     for (void* p : {(void*)ops, (void*)tasks, (void*)events, (void*)qoff, (void*)qents, (void*)fat})
@@ -139,7 +137,7 @@ int variant_for(const DevGraph* dg) {
   const int32_t* h = dg->g.header.data();
   const int batch = h[H_BATCH], tile_m = h[H_TILE_M];
   if (h[H_PATH] == P_FMA) return batch <= 1 ? 0 : batch <= 2 ? 1 : batch <= 4 ? 2 : 3;
-  return dg->wide ? dev::V_WHOLE : tile_m <= 16 ? 4 : tile_m <= 32 ? 5 : 6;
+  return whole_batch_tiles(dg->run) ? dev::V_WHOLE : tile_m <= 16 ? 4 : tile_m <= 32 ? 5 : 6;
 }
 int launch_persistent(DevGraph* dg, dev::Params& P, int n_cu, hipStream_t st) {
   const int v = variant_for(dg);
@@ -267,18 +265,6 @@ struct fleet {
 
 namespace {
 
-// bytes of one region of the graph's split-K partial sums: [k-slice][unit][m-tile][blocks x 256] fp32 of the largest operator
-size_t gpart_bytes(const Graph& g) {
-  size_t gp = 0;
-  for (int i = 0; i < g.n_ops(); ++i) {
-    const int32_t* o = &g.ops[(size_t)i * OP_WORDS];
-    if (o[O_BODY] != B_GEMM || o[O_PATH] != P_MFMA) continue;
-    const size_t ks = std::max(1, (o[O_AUX2] >> 16) & 15), nb = o[O_EPI] == E_SWIGLU_BF16 ? 2 : 1;
-    if (ks > 1) gp = std::max(gp, ks * nb * (size_t)o[O_N_UNITS] * o[O_M_TILES] * mfma_blocks(o[O_TILE_M]) * 256 * 4);
-  }
-  return align_up(gp);
-}
-
 // Working memory of one launch of graph dg besides the counter block, carved from `base` (may be
 // null: sizes only).  Returns the bytes needed.
 size_t work_layout(const fleet* f, const DevGraph* dg, char* base, Work* w) {
@@ -288,7 +274,7 @@ size_t work_layout(const fleet* f, const DevGraph* dg, char* base, Work* w) {
   const size_t NQKV = (size_t)(s.n_q_heads + 2 * s.n_kv_heads) * s.head_dim, QD = (size_t)s.n_q_heads * s.head_dim;
   const size_t grp = s.n_q_heads / s.n_kv_heads, S = std::max(1, g.header[H_N_SPLITS]);
   auto pad256 = [](size_t k) { return (k + 255) / 256 * 256; };
-  const size_t gp = gpart_bytes(g);
+  const size_t gp = align_up((size_t)gpart_bytes(g));
   const size_t regions = s.sched_mode == FLEET_SCHED_UNAWARE ? 1 : dev::MAX_XCD;
   size_t off = 0;
   auto take = [&](size_t bytes) { char* p = base ? base + off : nullptr; off += align_up(bytes); return p; };
@@ -416,54 +402,10 @@ int resolve_weight(const fleet* f, int wkind, int layer, const void* const* gemm
   return FLEET_OK;
 }
 
-// Batches of 65 to 128 rows under the cooperative schedule, where the caller leaves the tile height to the library: the graph
-// has two m-tiles of up to 64 rows per GEMM, and its chiplet-tasks are carried out in tiles of the whole batch
-// (gemm_tall_tile<8>).  Two m-tiles mean that every weight is taken in twice: one 8B layer at batch 100 / KV 100-1000 222 us that way,
-// 193 with whole tiles.  It takes weights that are worth it, 128 KB a worker: two layers of a model with hidden 1024 and FFN 3072 (48 KB) at batch 128
-// take 132 us with two m-tiles and 153 with whole tiles, whose split sums cost more than the weights.  An explicit height, the other schedules (whose tasks name an
-// m-tile) and the ablation without the streaming hint keep the 64-row tiles.
-bool wide_tiles(const Graph& g, int tile_m, int flags, int n_workers) {
-  if ((flags & FLEET_FLAG_NO_STREAM) || g.header[H_PATH] != P_MFMA || g.header[H_SCHED] != FLEET_SCHED_COOPERATIVE || tile_m != 0 || g.header[H_M_TILES] < 2) return false;
-  int64_t most = 0;
-  for (int i = 0; i < g.n_ops(); ++i) {
-    const int32_t* o = &g.ops[(size_t)i * OP_WORDS];
-    if (o[O_BODY] == B_GEMM && o[O_WKIND] != W_LM) most = std::max(most, (int64_t)o[O_K] * o[O_N] * (o[O_EPI] == E_SWIGLU_BF16 ? 4 : 2));
-  }
-  return most / n_workers >= 128 * 1024;
-}
-// an operator as its chiplet-tasks carry it out in whole-batch tiles: one m-tile, a plan of its own.  Its partial sums (a region per XCD,
-// only the XCD's own units) stay within part_bytes; where repetitions may overlap, k is only split if the graph's order counts on it.
-void widen_op(int32_t* o, int sched_flags, int n_xcd, int n_workers, size_t part_bytes, bool in_order) {
-  if (o[O_BODY] != B_GEMM) return;
-  const int nb = o[O_EPI] == E_SWIGLU_BF16 ? 2 : 1, mtb = (o[O_BATCH] + 15) / 16, ks = (o[O_AUX2] >> 16) & 15;
-  const bool split = !(sched_flags & FLEET_FLAG_NO_SPLITK) && o[O_N_UNITS] <= GEMM_TILE_COUNTERS && (in_order || ks > 1);
-  const MfmaPlan pl = plan_wide((o[O_N_UNITS] + n_xcd - 1) / n_xcd, n_workers / n_xcd, o[O_K], nb, mtb, split, (int64_t)nb * dev::variant_mt(dev::V_WHOLE), (int64_t)(part_bytes / 1024));
-  o[O_AUX2] = (o[O_AUX2] & ~((15 << 12) | (15 << 16) | (1 << 21))) | (pl.G << 12) | (pl.KS << 16);
-  o[O_M_TILES] = 1;
-  o[O_TILE_M] = 16 * dev::variant_mt(dev::V_WHOLE);
-}
-
-// May an MFMA GEMM's chiplet-task invalidate the caches of its XCD before it waits for its input instead of afterwards (FAT_INV)?
-// Old lines of the input are in those caches because (1) the XCD's workers read the buffer's contents before, or (2) they wrote parts of a line, or wrote
-// all of it some time ago.  After the invalidate none may appear:
-// (1) the last stage that read the buffer is over when the worker gets here.  It comes from the chiplet-task before on its queue (stage
-//     prev_stage, or from the start of the launch), and that task's wait was for the stage in front of prev_stage: everything up to there is over.
-// (2) what the XCD still writes to the buffer are whole lines: a line of 128 bytes comes from one XCD.  True of the SwiGLU products (a line is 8 rows by 8 features, a
-//     unit's tile all of its 16 features), of the norm by operand blocks, of the attention output where a kv head's sequences share an XCD (8 rows by 8
-//     features of one head), and of the fp32 residual rows where every XCD's units of 64 bytes a row begin on a line.
-// (gemm_reads: (buffer, stage) of every GEMM task's input)
-bool early_invalidate(const std::set<std::pair<int, int>>& gemm_reads, const int32_t* op, int stage, int prev_stage, int nkv, int flags, int n_xcd) {
-  const int in = op[O_IN_BUF];
-  if (op[O_PATH] != P_MFMA) return false;
-  const auto read = gemm_reads.lower_bound({in, prev_stage});
-  if (read != gemm_reads.end() && read->first == in && read->second < stage) return false;
-  switch (in) {
-    case BUF_N: return dev::norm_by_blocks(op[O_K]);
-    case BUF_X: return op[O_K] % (32 * n_xcd) == 0;
-    case BUF_ATT: return nkv % n_xcd == 0;
-    case BUF_H: return !(flags & FLEET_FLAG_UNFUSED_SILU);
-    default: return false;
-  }
+RunInfo run_info(const fleet* f, const DevInfo& info, int tile_m, int flags, size_t part_bytes) {
+  RunInfo ri = {info.n_xcd, info.n_cu, {}, tile_m, flags, f ? f->shape.n_kv_heads : 0, f != nullptr, (int64_t)part_bytes};
+  for (int x = 0; x < dev::MAX_XCD; ++x) ri.per_xcd[x] = info.per_xcd[x];
+  return ri;
 }
 
 // (tile_m: as the caller asked for; part_bytes: one region of partial sums)
@@ -471,25 +413,13 @@ int upload_graph(DevGraph* dg, const fleet* f, const void* const* gemm_copies, c
   const Graph& g = dg->g;
   const int n_xcd = info.n_xcd;
   int rc;
-  dg->wide = wide_tiles(g, tile_m, flags, info.n_cu);
+  dg->run = run_graph(g, run_info(f, info, tile_m, flags, part_bytes));
+  const Graph& r = dg->run;
   if ((rc = upload(&dg->ops, g.ops.data(), g.ops.size() * 4))) return rc;
   if ((rc = upload(&dg->tasks, g.tasks.data(), g.tasks.size() * 4))) return rc;
   if ((rc = upload(&dg->events, g.events.data(), g.events.size() * 4))) return rc;
   if ((rc = upload(&dg->qoff, g.qoff.data(), g.qoff.size() * 4))) return rc;
-  // The tasks of a norm stage go to the XCD's highest ranks where the QKV stage behind it leaves those idle (register-resident
-  // tiles, one per worker from rank 0 up): a worker that ran a norm task first would request its weights late and end the stage late.  (The
-  // builder does so itself up to four tasks per XCD.  With six and eight: two 8B layers at batch 48 318 -> 306 us, batch 64 351 -> 342.)
-  std::vector<int32_t> qents = g.qents;
-  for (int x = 0; x < n_xcd; ++x)
-    for (int qi = g.qoff[x]; qi + 1 < g.qoff[x + 1]; ++qi) {
-      int32_t* e = &qents[(size_t)qi * QENT_WORDS];
-      const int32_t *nt = &g.tasks[(size_t)e[Q_FIRST] * TASK_WORDS], *gt = &g.tasks[(size_t)e[QENT_WORDS + Q_FIRST] * TASK_WORDS];
-      const int32_t *no = &g.ops[(size_t)nt[T_OP] * OP_WORDS], *go = &g.ops[(size_t)gt[T_OP] * OP_WORDS];
-      if (e[Q_DIST] != D_XCD_RR || no[O_BODY] != B_RMSNORM || go[O_WKIND] != W_QKV || gt[T_SCOPE] != S_CHIPLET || !((go[O_AUX2] >> 21) & 1)) continue;
-      const int G = std::max(1, (go[O_AUX2] >> 12) & 15);
-      if (e[Q_COUNT] + (gt[T_A1] + G - 1) / G <= info.per_xcd[x]) e[Q_DIST] = D_XCD_RR_TOP;
-    }
-  if ((rc = upload(&dg->qents, qents.data(), qents.size() * 4))) return rc;
+  if ((rc = upload(&dg->qents, r.qents.data(), r.qents.size() * 4))) return rc;
   std::vector<const void*> w(g.n_ops()), w2(g.n_ops());
   for (int i = 0; i < g.n_ops(); ++i) {
     const int32_t* o = &g.ops[(size_t)i * OP_WORDS];
@@ -507,10 +437,9 @@ int upload_graph(DevGraph* dg, const fleet* f, const void* const* gemm_copies, c
   std::vector<int32_t> fat((size_t)g.n_tasks() * dev::FAT_WORDS, 0);
   for (int t = 0; t < g.n_tasks(); ++t) {
     int32_t* d = &fat[(size_t)t * dev::FAT_WORDS];
-    const int32_t* tw = &g.tasks[(size_t)t * TASK_WORDS];
+    const int32_t* tw = &r.tasks[(size_t)t * TASK_WORDS];
     memcpy(d, tw, TASK_WORDS * 4);
-    memcpy(d + TASK_WORDS, &g.ops[(size_t)tw[T_OP] * OP_WORDS], OP_WORDS * 4);
-    if (dg->wide) widen_op(d + TASK_WORDS, flags, n_xcd, info.n_cu, part_bytes, f != nullptr);
+    memcpy(d + TASK_WORDS, &r.ops[(size_t)tw[T_OP] * OP_WORDS], OP_WORDS * 4);
     memcpy(d + dev::FAT_W, &w[tw[T_OP]], sizeof(void*));
     memcpy(d + dev::FAT_W2, &w2[tw[T_OP]], sizeof(void*));
     d[dev::FAT_ID] = t;
@@ -523,36 +452,6 @@ int upload_graph(DevGraph* dg, const fleet* f, const void* const* gemm_copies, c
       for (int t = e[Q_FIRST]; t < e[Q_FIRST] + e[Q_COUNT]; ++t) {
         fat[(size_t)t * dev::FAT_WORDS + dev::FAT_GROUP] = e[Q_COUNT];
         fat[(size_t)t * dev::FAT_WORDS + dev::FAT_POS] = t - e[Q_FIRST];
-      }
-    }
-  // O and down projections: the rows they add to are complete when the stage in front of theirs starts.  The workers of an XCD
-  // know that they are if they run a task of that stage (a model with few FFN units gives some XCDs none of gate/up: their
-  // workers come to the down projection straight from O, whose other XCDs may still be writing)
-  auto stage_key = [&](int xcd, int layer, int wkind) { return ((int64_t)xcd * (MAX_LAYERS + 1) + layer) * 32 + wkind; };
-  std::set<int64_t> runs;
-  auto op_of = [&](int t) { return &g.ops[(size_t)g.tasks[(size_t)t * TASK_WORDS + T_OP] * OP_WORDS]; };
-  for (int pass = 0; pass < 2; ++pass)
-    for (int t = 0; t < g.n_tasks(); ++t) {
-      const int32_t *tw = &g.tasks[(size_t)t * TASK_WORDS], *op = op_of(t);
-      if (tw[T_SCOPE] != S_CHIPLET || op[O_BODY] != B_GEMM) continue;
-      if (pass == 0) runs.insert(stage_key(tw[T_XCD], op[O_LAYER], op[O_WKIND]));
-      else if (op[O_WKIND] == W_O || op[O_WKIND] == W_DOWN)
-        fat[(size_t)t * dev::FAT_WORDS + dev::FAT_HINTS] = runs.count(stage_key(tw[T_XCD], op[O_LAYER], op[O_WKIND] == W_O ? W_QKV : W_GU)) ? dev::FAT_EARLY : 0;
-    }
-  std::set<std::pair<int, int>> gemm_reads;
-  if (f)
-    for (int t = 0; t < g.n_tasks(); ++t)
-      if (op_of(t)[O_BODY] == B_GEMM) gemm_reads.insert({op_of(t)[O_IN_BUF], g.tasks[(size_t)t * TASK_WORDS + T_STAGE]});
-  if (f)
-    for (int x = 0; x < n_xcd; ++x) {
-      int prev_stage = 0;   // (no GEMM is in stage 0)
-      for (int qi = g.qoff[x]; qi < g.qoff[x + 1]; ++qi) {
-        const int32_t* e = &g.qents[(size_t)qi * QENT_WORDS];
-        if (e[Q_DIST] != D_CHIPLET) continue;
-        const int stage = g.tasks[(size_t)e[Q_FIRST] * TASK_WORDS + T_STAGE];
-        if (early_invalidate(gemm_reads, op_of(e[Q_FIRST]), stage, prev_stage, f->shape.n_kv_heads, flags, n_xcd))
-          fat[(size_t)e[Q_FIRST] * dev::FAT_WORDS + dev::FAT_HINTS] |= dev::FAT_INV;
-        prev_stage = stage;
       }
     }
   if ((rc = upload(&dg->fat, fat.data(), fat.size() * 4))) return rc;
@@ -799,7 +698,7 @@ int fleet_create(const fleet_shape_t* shape, const fleet_weights_t* w, fleet_t**
       std::unique_ptr<DevGraph> dg(new (std::nothrow) DevGraph());
       if (!dg) return FLEET_ENOMEM;
       dg->g = build_decode_graph(f->shape, b, f->info.n_xcd, f->info.n_cu, loop != 0, f->fma_max);
-      if ((rc = upload_graph(dg.get(), f.get(), nullptr, f->info, shape->tile_m, shape->flags, gpart_bytes(dg->g)))) return rc;
+      if ((rc = upload_graph(dg.get(), f.get(), nullptr, f->info, shape->tile_m, shape->flags, align_up((size_t)gpart_bytes(dg->g))))) return rc;
       f->work_bytes = std::max(f->work_bytes, work_layout(f.get(), dg.get(), nullptr, nullptr));
       f->ctr_set_words = std::max(f->ctr_set_words, ctr_set_words(dg.get()));
       (loop ? f->graphs_loop : f->graphs).push_back(std::move(dg));
@@ -988,6 +887,25 @@ int fleet_graph_dump(fleet_t* f, int32_t batch, void* buf, size_t* len) {
   DevGraph* dg = pick_graph(f, batch, false);
   if (!dg) return FLEET_EINVAL;
   return copy_words(dg->g.serialize(), buf, len);
+}
+
+int fleet_graph_build_run(const fleet_shape_t* shape, int32_t batch, int32_t n_xcd, int32_t n_workers, void* buf, size_t* len) {
+  if (!shape || !len || batch < 1 || n_xcd < 1 || n_xcd > dev::MAX_XCD || n_workers < n_xcd) return FLEET_EINVAL;
+  int rc = check_shape(*shape);
+  if (rc) return rc;
+  if (batch > shape->max_batch) return FLEET_EINVAL;
+  const int fma_max = (shape->flags & FLEET_FLAG_PACKED_ONLY) ? 0 : fma_max_from_env();
+  const Graph g = build_decode_graph(*shape, batch, n_xcd, n_workers, false, fma_max);
+  RunInfo ri = {n_xcd, n_workers, {}, shape->tile_m, shape->flags, shape->n_kv_heads, true, (int64_t)align_up((size_t)gpart_bytes(g))};
+  for (int x = 0; x < n_xcd; ++x) ri.per_xcd[x] = n_workers / n_xcd + (x < n_workers % n_xcd ? 1 : 0);
+  return copy_words(run_graph(g, ri).serialize(), buf, len);
+}
+
+int fleet_graph_dump_run(fleet_t* f, int32_t batch, void* buf, size_t* len) {
+  if (!f || !len || batch < 1 || batch > f->shape.max_batch) return FLEET_EINVAL;
+  DevGraph* dg = pick_graph(f, batch, false);
+  if (!dg) return FLEET_EINVAL;
+  return copy_words(dg->run.serialize(), buf, len);
 }
 
 int fleet_trace_read(fleet_t* f, void* buf, size_t* len) {

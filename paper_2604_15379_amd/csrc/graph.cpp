@@ -3,6 +3,7 @@
 
 #include <algorithm>
 #include <cstring>
+#include <set>
 
 namespace fleetg {
 
@@ -509,6 +510,118 @@ Graph build_gemm_graph(int B, int K, int N, int sched_mode, int tile_m, int flag
   b.mark_all();
   b.g.xready.push_back(-1);
   return b.finish(0, tm, path, 1, mt);
+}
+
+int64_t gpart_bytes(const Graph& g) {
+  int64_t gp = 0;
+  for (int i = 0; i < g.n_ops(); ++i) {
+    const int32_t* o = &g.ops[(size_t)i * OP_WORDS];
+    if (o[O_BODY] != B_GEMM || o[O_PATH] != P_MFMA) continue;
+    const int64_t ks = std::max(1, (o[O_AUX2] >> 16) & 15), nb = o[O_EPI] == E_SWIGLU_BF16 ? 2 : 1;
+    if (ks > 1) gp = std::max(gp, ks * nb * o[O_N_UNITS] * o[O_M_TILES] * mfma_blocks(o[O_TILE_M]) * 256 * 4);
+  }
+  return gp;
+}
+
+// Batches of 65 to 128 rows under the cooperative schedule, where the caller leaves the tile height to the library: the graph
+// has two m-tiles of up to 64 rows per GEMM, and its chiplet-tasks are carried out in tiles of the whole batch
+// (gemm_tall_tile<8>).  Two m-tiles mean that every weight is taken in twice: one 8B layer at batch 100 / KV 100-1000 222 us that way,
+// 193 with whole tiles.  It takes weights that are worth it, 128 KB a worker: two layers of a model with hidden 1024 and FFN 3072 (48 KB) at batch 128
+// take 132 us with two m-tiles and 153 with whole tiles, whose split sums cost more than the weights.  An explicit height, the other schedules (whose tasks name an
+// m-tile) and the ablation without the streaming hint keep the 64-row tiles.
+static bool takes_whole_batch(const Graph& g, const RunInfo& info) {
+  const int32_t* h = g.header.data();
+  if ((info.flags & FLEET_FLAG_NO_STREAM) || h[H_PATH] != P_MFMA || h[H_SCHED] != FLEET_SCHED_COOPERATIVE || info.tile_m != 0 || h[H_M_TILES] < 2) return false;
+  int64_t most = 0;
+  for (int i = 0; i < g.n_ops(); ++i) {
+    const int32_t* o = &g.ops[(size_t)i * OP_WORDS];
+    if (o[O_BODY] == B_GEMM && o[O_WKIND] != W_LM) most = std::max(most, (int64_t)o[O_K] * o[O_N] * (o[O_EPI] == E_SWIGLU_BF16 ? 4 : 2));
+  }
+  return most / info.n_workers >= 128 * 1024;
+}
+// an operator as its chiplet-tasks carry it out in whole-batch tiles: one m-tile, a plan of its own.  Its partial sums (a region per XCD,
+// only the XCD's own units) stay within part_bytes; where repetitions may overlap, k is only split if the graph's order counts on it.
+static void widen_op(int32_t* o, const RunInfo& info) {
+  if (o[O_BODY] != B_GEMM) return;
+  const int nb = o[O_EPI] == E_SWIGLU_BF16 ? 2 : 1, mtb = (o[O_BATCH] + 15) / 16, ks = (o[O_AUX2] >> 16) & 15;
+  const bool split = !(info.flags & FLEET_FLAG_NO_SPLITK) && o[O_N_UNITS] <= GEMM_TILE_COUNTERS && (info.step || ks > 1);
+  const MfmaPlan pl = plan_wide((o[O_N_UNITS] + info.n_xcd - 1) / info.n_xcd, info.n_workers / info.n_xcd, o[O_K], nb, mtb, split, nb * WHOLE_BLOCKS, info.part_bytes / 1024);
+  o[O_AUX2] = (o[O_AUX2] & ~((15 << 12) | (15 << 16) | (1 << 21))) | (pl.G << 12) | (pl.KS << 16);
+  o[O_M_TILES] = 1;
+  o[O_TILE_M] = 16 * WHOLE_BLOCKS;
+}
+
+// May an MFMA GEMM's chiplet-task invalidate the caches of its XCD before it waits for its input instead of afterwards (HINT_INV)?
+// Old lines of the input are in those caches because (1) the XCD's workers read the buffer's contents before, or (2) they wrote parts of a line, or wrote
+// all of it some time ago.  After the invalidate none may appear:
+// (1) the last stage that read the buffer is over when the worker gets here.  It comes from the chiplet-task before on its queue (stage
+//     prev_stage, or from the start of the launch), and that task's wait was for the stage in front of prev_stage: everything up to there is over.
+// (2) what the XCD still writes to the buffer are whole lines: a line of 128 bytes comes from one XCD.  True of the SwiGLU products (a line is 8 rows by 8 features, a
+//     unit's tile all of its 16 features), of the norm by operand blocks, of the attention output where a kv head's sequences share an XCD (8 rows by 8
+//     features of one head), and of the fp32 residual rows where every XCD's units of 64 bytes a row begin on a line.
+// (gemm_reads: (buffer, stage) of every GEMM task's input)
+static bool early_invalidate(const std::set<std::pair<int, int>>& gemm_reads, const int32_t* op, int stage, int prev_stage, const RunInfo& info) {
+  const int in = op[O_IN_BUF];
+  if (op[O_PATH] != P_MFMA) return false;
+  const auto read = gemm_reads.lower_bound({in, prev_stage});
+  if (read != gemm_reads.end() && read->first == in && read->second < stage) return false;
+  switch (in) {
+    case BUF_N: return norm_by_blocks(op[O_K]);
+    case BUF_X: return op[O_K] % (32 * info.n_xcd) == 0;
+    case BUF_ATT: return info.n_kv_heads % info.n_xcd == 0;
+    case BUF_H: return !(info.flags & FLEET_FLAG_UNFUSED_SILU);
+    default: return false;
+  }
+}
+
+Graph run_graph(const Graph& g, const RunInfo& info) {
+  Graph r = g;
+  auto task = [&](int t) { return &r.tasks[(size_t)t * TASK_WORDS]; };
+  auto op_of = [&](int t) { return &r.ops[(size_t)task(t)[T_OP] * OP_WORDS]; };
+  const bool whole = takes_whole_batch(g, info);
+  r.header[H_RUN_TILE_M] = whole ? 16 * WHOLE_BLOCKS : g.header[H_TILE_M];
+  if (whole)
+    for (int i = 0; i < r.n_ops(); ++i) widen_op(&r.ops[(size_t)i * OP_WORDS], info);
+  // The tasks of a norm stage go to the XCD's highest ranks where the QKV stage behind it leaves those idle (register-resident
+  // tiles, one per worker from rank 0 up): a worker that ran a norm task first would request its weights late and end the stage late.  (The
+  // builder does so itself up to four tasks per XCD.  With six and eight: two 8B layers at batch 48 318 -> 306 us, batch 64 351 -> 342.)
+  for (int x = 0; x < info.n_xcd; ++x)
+    for (int qi = g.qoff[x]; qi + 1 < g.qoff[x + 1]; ++qi) {
+      int32_t* e = &r.qents[(size_t)qi * QENT_WORDS];
+      const int32_t *gt = task(e[QENT_WORDS + Q_FIRST]), *no = op_of(e[Q_FIRST]), *go = op_of(e[QENT_WORDS + Q_FIRST]);
+      if (e[Q_DIST] != D_XCD_RR || no[O_BODY] != B_RMSNORM || go[O_WKIND] != W_QKV || gt[T_SCOPE] != S_CHIPLET || !((go[O_AUX2] >> 21) & 1)) continue;
+      const int G = std::max(1, (go[O_AUX2] >> 12) & 15);
+      if (e[Q_COUNT] + (gt[T_A1] + G - 1) / G <= info.per_xcd[x]) e[Q_DIST] = D_XCD_RR_TOP;
+    }
+  // O and down projections: the rows they add to are complete when the stage in front of theirs starts.  The workers of an XCD
+  // know that they are if they run a task of that stage (a model with few FFN units gives some XCDs none of gate/up: their
+  // workers come to the down projection straight from O, whose other XCDs may still be writing)
+  auto stage_key = [&](int xcd, int layer, int wkind) { return ((int64_t)xcd * (MAX_LAYERS + 1) + layer) * 32 + wkind; };
+  std::set<int64_t> runs;
+  for (int pass = 0; pass < 2; ++pass)
+    for (int t = 0; t < r.n_tasks(); ++t) {
+      int32_t* tw = task(t);
+      const int32_t* op = op_of(t);
+      if (tw[T_SCOPE] != S_CHIPLET || op[O_BODY] != B_GEMM) continue;
+      if (pass == 0) runs.insert(stage_key(tw[T_XCD], op[O_LAYER], op[O_WKIND]));
+      else if ((op[O_WKIND] == W_O || op[O_WKIND] == W_DOWN) && runs.count(stage_key(tw[T_XCD], op[O_LAYER], op[O_WKIND] == W_O ? W_QKV : W_GU)))
+        tw[T_HINTS] |= HINT_EARLY;
+    }
+  if (!info.step) return r;
+  std::set<std::pair<int, int>> gemm_reads;
+  for (int t = 0; t < r.n_tasks(); ++t)
+    if (op_of(t)[O_BODY] == B_GEMM) gemm_reads.insert({op_of(t)[O_IN_BUF], task(t)[T_STAGE]});
+  for (int x = 0; x < info.n_xcd; ++x) {
+    int prev_stage = 0;   // (no GEMM is in stage 0)
+    for (int qi = g.qoff[x]; qi < g.qoff[x + 1]; ++qi) {
+      const int32_t* e = &r.qents[(size_t)qi * QENT_WORDS];
+      if (e[Q_DIST] != D_CHIPLET) continue;
+      int32_t* tw = task(e[Q_FIRST]);
+      if (early_invalidate(gemm_reads, op_of(e[Q_FIRST]), tw[T_STAGE], prev_stage, info)) tw[T_HINTS] |= HINT_INV;
+      prev_stage = tw[T_STAGE];
+    }
+  }
+  return r;
 }
 
 }  // namespace fleetg

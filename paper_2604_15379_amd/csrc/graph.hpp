@@ -32,7 +32,8 @@ constexpr int32_t MAGIC = 0x464c5447;  // "FLTG"
 // header word indices
 enum {
   H_MAGIC = 0, H_VERSION, H_N_OPS, H_N_TASKS, H_N_EVENTS, H_N_XCD, H_N_QENT, H_N_LAYERS,
-  H_BATCH, H_SCHED, H_TILE_M, H_PATH, H_N_SPLITS, H_N_WORKERS, H_M_TILES, H_TOTAL_WORDS
+  H_BATCH, H_SCHED, H_TILE_M, H_PATH, H_N_SPLITS, H_N_WORKERS, H_M_TILES, H_TOTAL_WORDS,
+  H_RUN_TILE_M   // run_graph: batch rows of the tiles that are carried out (the builder's graph: 0)
 };
 
 enum Body { B_INGEST = 0, B_RMSNORM = 1, B_GEMM = 2, B_ATTN = 3, B_SWIGLU = 4, B_FINAL = 5, B_ARGMAX = 6 };
@@ -90,7 +91,10 @@ constexpr int GEMV_LDS_X_BYTES = 96 * 1024;   // LDS the FMA path may fill with 
 //   GEMM CU-task      : A0 first unit, A1 unit count, A2 m-tile, A3 k-slice
 //   ATTN              : A0 batch row, A1 kv head, A2 split, A3 n_splits
 //   INGEST/RMSNORM/SWIGLU/FINAL/ARGMAX : A0 batch row
-enum { T_OP = 0, T_SCOPE, T_XCD, T_A0, T_A1, T_A2, T_A3, T_WAIT_EVENT, T_SIGNAL_EVENT, T_STAGE };
+// T_HINTS (run_graph): HINT_EARLY: the residual rows a chiplet-task adds to are complete before it waits (its workers have waited for a stage behind
+// them); HINT_INV: the caches may be invalidated before an MFMA GEMM's wait instead of after it
+enum { T_OP = 0, T_SCOPE, T_XCD, T_A0, T_A1, T_A2, T_A3, T_WAIT_EVENT, T_SIGNAL_EVENT, T_STAGE, T_HINTS };
+constexpr int HINT_EARLY = 1, HINT_INV = 2;
 // event word indices: threshold counts device-level signals (XCDs for a
 // two-level event, tasks for a direct one); n_tasks counts the signalling tasks
 enum { E_THRESHOLD = 0, E_KIND, E_XCD_MASK, E_N_TASKS };
@@ -119,6 +123,10 @@ MfmaPlan plan_mfma(int units_per_xcd, int workers_per_xcd, int K, int nb, int mt
 MfmaPlan plan_wide(int units_per_xcd, int workers_per_xcd, int K, int nb, int mtb, bool allow_split, int64_t part_kb, int64_t max_part_kb);
 // 16-row blocks of batch rows the MFMA kernel for tile height tile_m accumulates (1, 2 or 4)
 int mfma_blocks(int tile_m);
+constexpr int WHOLE_BLOCKS = 8;     // the same of the kernel for tiles of the whole batch
+// Are the norm stages of the MFMA kernels done by operand blocks (body_rmsnorm_blocks)?  Sums of squares are read four at
+// a time.
+constexpr bool norm_by_blocks(int hidden) { return hidden % 64 == 0; }
 // largest batch that runs the FMA GEMV kernels (larger batches run the MFMA kernels): 1, or
 // what the environment variable FLEET_FMA_MAX_BATCH (0..8) says.  Read once by whoever owns
 // a set of graphs (fleet_create, fleet_gemm, fleet_graph_build) and handed to the builders, so
@@ -142,6 +150,13 @@ Graph build_decode_graph(const fleet_shape_t& s, int batch, int n_xcd, int n_wor
 // `reps` GEMM device-tasks y = x W^T (rep i reads weight copy i % n_copies)
 Graph build_gemm_graph(int B, int K, int N, int sched_mode, int tile_m, int flags, int reps,
                        int n_copies, int n_xcd, int n_workers, int fma_max);
+// bytes of one region of the graph's split-K partial sums: [k-slice][unit][m-tile][blocks x 256] fp32 of the largest operator
+int64_t gpart_bytes(const Graph& g);
+// The graph as the workers carry it out, in the builder's words: GEMMs in tiles of the whole batch, norm tasks on the ranks that
+// their XCD leaves idle, hints to the tasks.  step: a decode step (false: repetitions of one GEMM, which may overlap); part_bytes: one region of partial sums
+struct RunInfo { int n_xcd, n_workers, per_xcd[8], tile_m, flags, n_kv_heads; bool step; int64_t part_bytes; };   // (tile_m as the caller asked for)
+Graph run_graph(const Graph& g, const RunInfo& info);
+inline bool whole_batch_tiles(const Graph& run) { return run.header[H_RUN_TILE_M] == 16 * WHOLE_BLOCKS; }
 // marks per XCD of a decode graph with n_layers layers
 inline int n_marks(int n_layers) { return n_layers + 4; }
 

@@ -444,6 +444,149 @@ def test_graph_invariants(batch, sched):
         assert op[8] == -(-batch // op[9]) and op[5] == op[6] * op[7]
 
 
+# ------------------------------------------------------------------ the graph as the workers carry it out
+QWEN = si.qwen3_8b_shape(128, 513, n_layers=2).asdict()
+HINT_EARLY, HINT_INV = 1, 2
+GB_SWIGLU = 2                # epilogue of the gate|up GEMM
+
+
+def _both(sh, batch, sched=0, tile_m=0, flags=0, n_xcd=8, n_workers=256):
+    args = (sh, batch, n_xcd, n_workers, sched, tile_m, flags)
+    return F.parse_graph(F.fleet_graph_build(*args)), F.parse_graph(F.fleet_graph_build_run(*args))
+
+
+def _plan(op):
+    return int(op[15]) >> 12 & 15, max(1, int(op[15]) >> 16 & 15)
+
+
+@pytest.mark.parametrize("sched,tile_m,flags", [(0, 0, 0), (0, 32, 0), (1, 0, 0), (2, 16, 0), (0, 0, 64), (0, 0, 32), (0, 0, 256)])
+@pytest.mark.parametrize("batch", [1, 8, 48, 64, 65, 100, 128])
+def test_run_graph_keeps_tasks_events_and_stages(batch, sched, tile_m, flags):
+    """What runs differs from what the builder builds in the operators of whole-batch tiles (one
+    m-tile, units per tile and k-slices), in the direction norm tasks are dealt in, and by hints."""
+    for sh in (QWEN, si.reduced_shape(max_batch=128, n_layers=2, vocab=2064).asdict()):
+        g, r = _both(sh, batch, sched, tile_m, flags)
+        for k in ("events", "qoff", "marks", "xready"):
+            assert np.array_equal(g[k], r[k]), k
+        assert np.array_equal(g["tasks"][:, :10], r["tasks"][:, :10]) and (g["tasks"][:, 10:] == 0).all()
+        assert np.array_equal(g["qents"][:, [0, 1, 3]], r["qents"][:, [0, 1, 3]])
+        changed = r["qents"][:, 2] != g["qents"][:, 2]
+        assert (g["qents"][changed, 2] == 1).all() and (r["qents"][changed, 2] == 3).all()
+        whole = r["header"]["run_tile_m"] == 128
+        assert g["header"]["run_tile_m"] == 0 and (whole or r["header"]["run_tile_m"] == g["header"]["tile_m"])
+        if not whole:
+            assert np.array_equal(g["ops"], r["ops"])
+        else:
+            assert batch > 64 and sched == 0 and tile_m == 0
+            same = [c for c in range(16) if c not in (8, 9, 15)]
+            assert np.array_equal(g["ops"][:, same], r["ops"][:, same])
+
+
+@pytest.mark.parametrize("flags", [0, 32, 256])
+@pytest.mark.parametrize("batch", [65, 81, 100, 128])
+def test_plans_of_whole_batch_tiles(batch, flags):
+    """One m-tile of 128 rows, no more row blocks than a tile has registers for, whole k-steps per
+    wavefront in a k-slice, and no more partial sums per XCD than the builder's own plan has room for."""
+    for sh in (QWEN, dict(QWEN, hidden=3072, ffn=8192, n_q_heads=24), dict(QWEN, hidden=2560, ffn=9728),
+               dict(QWEN, hidden=4064, ffn=11104, vocab=151936)):
+        g, r = _both(sh, batch, flags=flags)
+        assert r["header"]["run_tile_m"] == 128
+        region = 0
+        for op in g["ops"]:
+            if op[0] == GEMM and _plan(op)[1] > 1:
+                region = max(region, _plan(op)[1] * (2 if op[2] == GB_SWIGLU else 1) * int(op[7] * op[8]) * 4 * 1024)
+        for op in r["ops"]:
+            if op[0] != GEMM:
+                continue
+            nb = 2 if op[2] == GB_SWIGLU else 1
+            G, KS = _plan(op)
+            assert op[8] == 1 and op[9] == 128 and not op[15] >> 21 & 1
+            assert 1 <= G * nb <= 6 and KS in (1, 2, 4, 8)
+            if KS > 1:
+                assert not flags & 32 and op[4] % (128 * KS) == 0 and op[7] <= 4096
+                assert KS * nb * -(-int(op[7]) // 8) * 8 * 1024 <= region    # an XCD's units, 8 blocks of 1 KB each
+
+
+@pytest.mark.parametrize("sched,flags", [(0, 0), (0, 4), (0, 256), (2, 0), (1, 0)])
+@pytest.mark.parametrize("batch", [2, 17, 40, 64, 100])
+@pytest.mark.parametrize("model", ["8b", "reduced", "odd"])
+def test_early_invalidates_leave_no_old_line(model, batch, sched, flags):
+    """A GEMM with HINT_INV invalidates its XCD's caches before it waits.  Then (1) every stage that reads
+    its input is over when a worker gets there: it lies in front of the stage of the XCD's chiplet-task
+    before; (2) every 128-byte line of the input that the stage in front writes comes from one XCD only.
+    The writers are derived here from the tasks."""
+    sh = {"8b": QWEN, "reduced": si.reduced_shape(max_batch=128, n_layers=2, vocab=2064).asdict(),
+          "odd": dict(QWEN, hidden=1504, ffn=2080, n_q_heads=12, n_kv_heads=3)}[model]
+    g, r = _both(sh, batch, sched, flags=flags)
+    ops, tasks = r["ops"], r["tasks"]
+    reads = {}
+    for t in tasks:
+        op = ops[t[0]]
+        if op[0] == GEMM:
+            reads.setdefault(int(op[10]), set()).add(int(t[9]))
+    hinted = 0
+    for x in range(8):
+        prev = 0
+        for e in r["qents"][r["qoff"][x]:r["qoff"][x + 1]]:
+            if e[2] != 0:
+                continue
+            t = tasks[e[0]]
+            op = ops[t[0]]
+            if t[10] & HINT_INV:
+                hinted += 1
+                assert not [s for s in reads[int(op[10])] if prev <= s < t[9]]
+                owner = {}
+                for w in tasks[(tasks[:, 9] < t[9]) & (ops[tasks[:, 0], 11] == op[10])]:
+                    wo = ops[w[0]]
+                    if wo[1] != op[1] and wo[0] != INGEST:
+                        continue                                   # (this layer's writers, and the ingest stage)
+                    for line in _lines(wo, w, batch, sh):
+                        assert owner.setdefault((int(w[9]), line), int(w[2])) == int(w[2]), (int(wo[13]), line)
+                assert owner or op[1] > 0 or op[13] == WK["LM"]
+            prev = int(t[9])
+    assert hinted == 0 if sched == 1 else hinted > 0 or model == "odd"
+
+
+def _lines(op, task, batch, sh):
+    """128-byte lines of the operator's output buffer that a task writes: ('x', row, i) of a row-major
+    fp32 row; ('b', block of 8 rows, i) of operand blocks, 8 features each."""
+    H = sh["hidden"]
+    rows8 = range(-(-batch // 8))
+    if op[0] == GEMM and op[11] == BUF["X"]:
+        return {("x", b, u * 16 // 32) for b in range(batch) for u in range(task[3], task[3] + task[4])}
+    if op[0] == GEMM and op[11] == BUF["H"]:
+        tiles = rows8 if task[6] == 0 else range(8 * (task[6] - 1), min(8 * task[6], len(rows8)))   # (M-split: an m-tile of 64 rows)
+        return {("b", r8, f) for r8 in tiles for u in range(task[3], task[3] + task[4]) for f in (2 * u, 2 * u + 1)}
+    if op[0] == INGEST:
+        return {("x", int(task[3]), i) for i in range(H // 32)}
+    if op[0] == ATTN:
+        grp = sh["n_q_heads"] // sh["n_kv_heads"]
+        lo = int(task[4]) * grp * 16
+        return {("b", int(task[3]) // 8, f) for f in range(lo, lo + grp * 16)}
+    if op[0] in (RMSNORM, FINAL):      # task i of the step's n: 16-row block i mod m, k-steps of 32 features by the wavefronts
+        n, i = batch, int(task[3])
+        m = -(-n // 16)
+        nj = (n - i % m + m - 1) // m
+        return {("b", 2 * (i % m) + h, 4 * s + f) for wave in range(8) for s in range(i // m * 8 + wave, H // 32, nj * 8)
+                for h in (0, 1) for f in range(4)}
+    return set()
+
+
+@pytest.mark.parametrize("batch,top", [(20, True), (48, True), (64, True), (128, False)])
+def test_norm_tasks_run_on_ranks_that_qkv_leaves_idle(batch, top):
+    """Register-resident QKV tiles (8B shape: 24 per XCD) and the norm tasks of up to 64 rows (8 per XCD)
+    fit the 32 workers; where they do not, or nothing is resident, norm tasks are dealt from rank 0."""
+    g, r = _both(QWEN, batch)
+    ln1 = [i for i, op in enumerate(r["ops"]) if op[0] == RMSNORM and op[13] == WK["LN1"]]
+    ln2 = [i for i, op in enumerate(r["ops"]) if op[0] == RMSNORM and op[13] == WK["LN2"]]
+    dist = {int(r["tasks"][e[0], 0]): int(e[2]) for e in r["qents"]}
+    assert all(dist[i] == (3 if top else 1) for i in ln1) and all(dist[i] == 1 for i in ln2)
+    if batch == 64:      # 16 workers per XCD: 24 tiles do not even fit one each
+        r16 = _both(QWEN, batch, n_workers=128)[1]
+        dist = {int(r16["tasks"][e[0], 0]): int(e[2]) for e in r16["qents"]}
+        assert all(dist[i] == 1 for i in ln1)
+
+
 def test_paper_task_counts_and_partition_pointers():
     """Fleet's graph at bs=1: one CU-task per norm and eight chiplet-tasks per GEMM; the
     partition of chiplet k starts k*(N/8) rows into the weight matrix."""
