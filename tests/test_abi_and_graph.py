@@ -516,7 +516,7 @@ def test_early_invalidates_leave_no_old_line(model, batch, sched, flags):
     before; (2) every 128-byte line of the input that the stage in front writes comes from one XCD only.
     The writers are derived here from the tasks."""
     sh = {"8b": QWEN, "reduced": si.reduced_shape(max_batch=128, n_layers=2, vocab=2064).asdict(),
-          "odd": dict(QWEN, hidden=1504, ffn=2080, n_q_heads=12, n_kv_heads=3)}[model]
+          "odd": dict(QWEN, hidden=1600, ffn=2080, n_q_heads=12, n_kv_heads=3)}[model]
     g, r = _both(sh, batch, sched, flags=flags)
     ops, tasks = r["ops"], r["tasks"]
     reads = {}
