@@ -524,20 +524,30 @@ int64_t gpart_bytes(const Graph& g) {
 }
 
 // Batches of 65 to 128 rows under the cooperative schedule, where the caller leaves the tile height to the library: the graph
-// has two m-tiles of up to 64 rows per GEMM, and its chiplet-tasks are carried out in tiles of the whole batch
-// (gemm_tall_tile<8>).  Two m-tiles mean that every weight is taken in twice: one 8B layer at batch 100 / KV 100-1000 222 us that way,
-// 193 with whole tiles.  It takes weights that are worth it, 128 KB a worker: two layers of a model with hidden 1024 and FFN 3072 (48 KB) at batch 128
-// take 132 us with two m-tiles and 153 with whole tiles, whose split sums cost more than the weights.  An explicit height, the other schedules (whose tasks name an
-// m-tile) and the ablation without the streaming hint keep the 64-row tiles.
+// has two m-tiles of up to 64 rows per GEMM, and its chiplet-tasks may be carried out in tiles of the whole batch
+// (gemm_tall_tile<8>).  Two m-tiles mean that every weight is taken in twice; a whole tile has twice the sums to split and to add.  The operator
+// with the most weights (gate/up) decides, by its two-m-tile plan:
+//   * its k is not split and no worker has more than one tile: two m-tiles, a whole-batch plan would have to split k.  Two layers, KV 100-600, two m-tiles and
+//     whole tiles: hidden 2048, FFN 6144 (192 KB a worker) 188 and 196 us at batch 65, 230 and 247 at 128; FFN 4096 185 and 188, 227 and 242; hidden 2560, FFN 6144 197 and
+//     192, 230 and 238; a 4096 x 8192 GEMM at batch 96 24.6 and 30.0 us, 2048 x 12288 18.3 and 20.0;
+//   * otherwise whole tiles: hidden 2048, FFN 7168 (224 KB; 38 tiles for 32 workers) 217 and 203, 263 and 252; hidden 2560, FFN 7168 242 and 202, 275 and 244; one 8B layer at batch 100 /
+//     KV 100-1000 222 and 193; a 12288 x 4096 GEMM at batch 96 34.3 and 32.1, 4096 x 4096 (128 KB) 18.2 and 16.9, 1024 x 16384 20.8 and 15.3;
+//   * below 128 KB a worker the split sums cost more than the weights: hidden 1024, FFN 3072 (48 KB) at batch 128 132 and 153.
+// An explicit height, the other schedules (whose tasks name an m-tile) and the ablation without the streaming hint keep the 64-row tiles.
 static bool takes_whole_batch(const Graph& g, const RunInfo& info) {
   const int32_t* h = g.header.data();
   if ((info.flags & FLEET_FLAG_NO_STREAM) || h[H_PATH] != P_MFMA || h[H_SCHED] != FLEET_SCHED_COOPERATIVE || info.tile_m != 0 || h[H_M_TILES] < 2) return false;
+  const int32_t* top = nullptr;
   int64_t most = 0;
   for (int i = 0; i < g.n_ops(); ++i) {
     const int32_t* o = &g.ops[(size_t)i * OP_WORDS];
-    if (o[O_BODY] == B_GEMM && o[O_WKIND] != W_LM) most = std::max(most, (int64_t)o[O_K] * o[O_N] * (o[O_EPI] == E_SWIGLU_BF16 ? 4 : 2));
+    if (o[O_BODY] != B_GEMM || o[O_WKIND] == W_LM) continue;
+    const int64_t bytes = (int64_t)o[O_K] * o[O_N] * (o[O_EPI] == E_SWIGLU_BF16 ? 4 : 2);
+    if (bytes > most) { most = bytes; top = o; }
   }
-  return most / info.n_workers >= 128 * 1024;
+  if (!top || most / info.n_workers < 128 * 1024) return false;
+  const int G = std::max(1, (top[O_AUX2] >> 12) & 15), KS = std::max(1, (top[O_AUX2] >> 16) & 15), ux = (top[O_N_UNITS] + info.n_xcd - 1) / info.n_xcd;
+  return KS > 1 || (ux + G - 1) / G * top[O_M_TILES] > info.n_workers / info.n_xcd;
 }
 // an operator as its chiplet-tasks carry it out in whole-batch tiles: one m-tile, a plan of its own.  Its partial sums (a region per XCD,
 // only the XCD's own units) stay within part_bytes; where repetitions may overlap, k is only split if the graph's order counts on it.

@@ -482,6 +482,25 @@ def test_run_graph_keeps_tasks_events_and_stages(batch, sched, tile_m, flags):
             assert np.array_equal(g["ops"][:, same], r["ops"][:, same])
 
 
+@pytest.mark.parametrize("hidden,ffn,whole", [(4096, 12288, True), (3072, 8192, True), (2560, 9728, True), (2048, 8192, True), (2560, 7168, True),
+                                              (2048, 7168, True),       # 38 two-m-tile tiles for 32 workers
+                                              (2048, 6144, False), (2560, 6144, False), (2048, 4096, False),   # one unsplit tile a worker
+                                              (1024, 8128, False),      # 127 KB of weights a worker, two tiles
+                                              (1024, 3072, False)])
+def test_which_steps_run_whole_batch_tiles(hidden, ffn, whole):
+    """Two m-tiles where the gate/up plan of two m-tiles gets by with one unsplit tile a worker, and for
+    small models; the batch, the schedule and an explicit tile height."""
+    sh = dict(QWEN, hidden=hidden, ffn=ffn)
+    def rows(batch, *args):
+        return _both(sh, batch, *args)[1]["header"]["run_tile_m"]
+
+    for batch in (65, 100, 128):
+        assert rows(batch) == (128 if whole else 64)
+        assert rows(batch, 1) == rows(batch, 2) == rows(batch, 0, 64) == 64
+        assert rows(batch, 0, 32) == 32
+    assert rows(64) == 64 and rows(33) == 48 and rows(8) == 16
+
+
 @pytest.mark.parametrize("flags", [0, 32, 256])
 @pytest.mark.parametrize("batch", [65, 81, 100, 128])
 def test_plans_of_whole_batch_tiles(batch, flags):
