@@ -1,6 +1,6 @@
 """Build the HIP library for gfx950 with hipcc (cross-compiles without a GPU).
 
-The persistent kernel exists in eight flavours (one translation unit each, see
+The persistent kernel exists in nine flavours (one translation unit each, see
 csrc/kernel_variant.hip); the objects are compiled in parallel and linked into
 libfleet.so next to this file.
 """
@@ -14,7 +14,7 @@ _PKG = os.path.dirname(os.path.abspath(__file__))
 _CSRC = os.path.join(_PKG, "csrc")
 _OBJ = os.path.join(_PKG, "_build")
 LIB_PATH = os.path.join(_PKG, "libfleet.so")
-N_VARIANTS = 8
+N_VARIANTS = 9
 _DEPS = [os.path.join(_CSRC, n) for n in ("fleet.hip", "graph.cpp", "kernel_variant.hip", "kernels.hip.inc",
                                           "aux_kernels.hip.inc", "graph.hpp")] + \
         [os.path.join(_PKG, "..", "include", "fleet.h")]

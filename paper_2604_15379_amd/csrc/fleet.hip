@@ -24,7 +24,7 @@
   extern template __global__ void fleet_persistent_kernel<V, false>(dev::Params);     \
   extern template __global__ void fleet_persistent_kernel<V, true>(dev::Params);
 FLEET_EXTERN_VARIANT(0) FLEET_EXTERN_VARIANT(1) FLEET_EXTERN_VARIANT(2) FLEET_EXTERN_VARIANT(3)
-FLEET_EXTERN_VARIANT(4) FLEET_EXTERN_VARIANT(5) FLEET_EXTERN_VARIANT(6) FLEET_EXTERN_VARIANT(7)
+FLEET_EXTERN_VARIANT(4) FLEET_EXTERN_VARIANT(5) FLEET_EXTERN_VARIANT(6) FLEET_EXTERN_VARIANT(7) FLEET_EXTERN_VARIANT(8)
 #undef FLEET_EXTERN_VARIANT
 
 // Workspace of fleet_decode_step_static, the entry point that allocates nothing: the
@@ -69,6 +69,7 @@ struct Work {
 
 struct DevGraph {
   Graph g, run;             // as built, as carried out (run_graph)
+  bool no_stream = false;   // FLEET_FLAG_NO_STREAM
   int32_t *ops = nullptr, *tasks = nullptr, *events = nullptr, *qoff = nullptr, *qents = nullptr;
   int32_t* fat = nullptr;   // [n_tasks][FAT_WORDS]: task words, op words, weight pointers, id
   int ctr_words = 0, gcnt_base = 0;   // words of counters (a set), first of the split-K tile counters
@@ -118,7 +119,8 @@ const void* kernel_variant(int v, bool paged = false) {
       case 4: return (const void*)fleet_persistent_kernel<4, true>;
       case 5: return (const void*)fleet_persistent_kernel<5, true>;
       case 6: return (const void*)fleet_persistent_kernel<6, true>;
-      default: return (const void*)fleet_persistent_kernel<7, true>;
+      case 7: return (const void*)fleet_persistent_kernel<7, true>;
+      default: return (const void*)fleet_persistent_kernel<8, true>;
     }
   }
   switch (v) {
@@ -129,7 +131,8 @@ const void* kernel_variant(int v, bool paged = false) {
     case 4: return (const void*)fleet_persistent_kernel<4>;
     case 5: return (const void*)fleet_persistent_kernel<5>;
     case 6: return (const void*)fleet_persistent_kernel<6>;
-    default: return (const void*)fleet_persistent_kernel<7>;
+    case 7: return (const void*)fleet_persistent_kernel<7>;
+    default: return (const void*)fleet_persistent_kernel<8>;
   }
 }
 // variant for a graph: FMA path by batch (1, 2, 4, 8), MFMA path by tile height
@@ -137,7 +140,8 @@ int variant_for(const DevGraph* dg) {
   const int32_t* h = dg->g.header.data();
   const int batch = h[H_BATCH], tile_m = h[H_TILE_M];
   if (h[H_PATH] == P_FMA) return batch <= 1 ? 0 : batch <= 2 ? 1 : batch <= 4 ? 2 : 3;
-  return whole_batch_tiles(dg->run) ? dev::V_WHOLE : tile_m <= 16 ? 4 : tile_m <= 32 ? 5 : 6;
+  if (whole_batch_tiles(dg->run)) return dev::V_WHOLE;
+  return tile_m <= 16 ? 4 : tile_m <= 32 ? 5 : h[H_M_TILES] > 1 || dg->no_stream ? dev::V_M_TILES : dev::V_TALL;
 }
 int launch_persistent(DevGraph* dg, dev::Params& P, int n_cu, hipStream_t st) {
   const int v = variant_for(dg);
@@ -415,6 +419,7 @@ int upload_graph(DevGraph* dg, const fleet* f, const void* const* gemm_copies, c
   int rc;
   dg->run = run_graph(g, run_info(f, info, tile_m, flags, part_bytes));
   const Graph& r = dg->run;
+  dg->no_stream = (flags & FLEET_FLAG_NO_STREAM) != 0;
   if ((rc = upload(&dg->ops, g.ops.data(), g.ops.size() * 4))) return rc;
   if ((rc = upload(&dg->tasks, g.tasks.data(), g.tasks.size() * 4))) return rc;
   if ((rc = upload(&dg->events, g.events.data(), g.events.size() * 4))) return rc;
