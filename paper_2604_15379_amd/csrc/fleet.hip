@@ -69,7 +69,6 @@ struct Work {
 
 struct DevGraph {
   Graph g, run;             // as built, as carried out (run_graph)
-  bool no_stream = false;   // FLEET_FLAG_NO_STREAM
   int32_t *ops = nullptr, *tasks = nullptr, *events = nullptr, *qoff = nullptr, *qents = nullptr;
   int32_t* fat = nullptr;   // [n_tasks][FAT_WORDS]: task words, op words, weight pointers, id
   int ctr_words = 0, gcnt_base = 0;   // words of counters (a set), first of the split-K tile counters
@@ -141,7 +140,7 @@ int variant_for(const DevGraph* dg) {
   const int batch = h[H_BATCH], tile_m = h[H_TILE_M];
   if (h[H_PATH] == P_FMA) return batch <= 1 ? 0 : batch <= 2 ? 1 : batch <= 4 ? 2 : 3;
   if (whole_batch_tiles(dg->run)) return dev::V_WHOLE;
-  return tile_m <= 16 ? 4 : tile_m <= 32 ? 5 : h[H_M_TILES] > 1 || dg->no_stream ? dev::V_M_TILES : dev::V_TALL;
+  return tile_m <= 16 ? 4 : tile_m <= 32 ? 5 : h[H_M_TILES] > 1 ? dev::V_M_TILES : dev::V_TALL;
 }
 int launch_persistent(DevGraph* dg, dev::Params& P, int n_cu, hipStream_t st) {
   const int v = variant_for(dg);
@@ -419,7 +418,6 @@ int upload_graph(DevGraph* dg, const fleet* f, const void* const* gemm_copies, c
   int rc;
   dg->run = run_graph(g, run_info(f, info, tile_m, flags, part_bytes));
   const Graph& r = dg->run;
-  dg->no_stream = (flags & FLEET_FLAG_NO_STREAM) != 0;
   if ((rc = upload(&dg->ops, g.ops.data(), g.ops.size() * 4))) return rc;
   if ((rc = upload(&dg->tasks, g.tasks.data(), g.tasks.size() * 4))) return rc;
   if ((rc = upload(&dg->events, g.events.data(), g.events.size() * 4))) return rc;

@@ -497,7 +497,7 @@ def test_which_steps_run_whole_batch_tiles(hidden, ffn, whole):
     for batch in (65, 100, 128):
         assert rows(batch) == (128 if whole else 64)
         assert rows(batch, 1) == rows(batch, 2) == rows(batch, 0, 64) == 64
-        assert rows(batch, 0, 32) == 32
+        assert rows(batch, 0, 32) == 32 and rows(batch, 0, 0, 64) == rows(batch)   # (64: no streaming hint)
     assert rows(64) == 64 and rows(33) == 48 and rows(8) == 16
 
 

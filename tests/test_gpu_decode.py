@@ -940,6 +940,18 @@ def test_whole_batch_tiles_in_a_step(batch):
     assert_close(low[0], got[0], "64-row tiles")
 
 
+@pytest.mark.parametrize("hidden,ffn", [(1024, 3072), (2048, 7168)])
+@pytest.mark.parametrize("batch", [1, 12, 24, 40, 64, 100])
+def test_streaming_hint_changes_no_bit(batch, hidden, ffn):
+    """FLEET_FLAG_NO_STREAM takes the cache hint off the weight loads and nothing else: the same tiles and
+    k-slices in every kernel flavour."""
+    sh = si.Shape(1, hidden, 16, 8, 128, ffn, 528, batch, 64)
+    m = Model(sh, seed=78, batch=batch, positions=np.random.default_rng(78).integers(0, 64, batch).astype(np.int32))
+    print(f"no streaming hint batch={batch} hidden={hidden}", flush=True)
+    a, b = m.run_gpu(), m.run_gpu(0, 0, F.FLAG_NO_STREAM)
+    assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+
+
 @pytest.mark.parametrize("sched", [0, 2])
 @pytest.mark.parametrize("batch,nkv,hidden,ffn", [(2, 8, 1024, 1024), (3, 2, 1088, 1024), (16, 8, 2048, 2048), (20, 8, 2048, 2048), (24, 2, 1024, 3072),
                                                   (40, 8, 2048, 2048), (48, 4, 1056, 96), (100, 8, 2048, 4096)])
