@@ -921,16 +921,30 @@ def test_steps_after_an_aborted_one(static):
         F.fleet_destroy(fresh)
 
 
+# 224 KB of gate/up weights a worker, more tiles of two m-tiles than workers: whole-batch tiles from 65 rows on
+def _whole_shape(n_layers, max_batch, max_seq, vocab=528):
+    return si.Shape(n_layers, 2048, 16, 8, 128, 7168, vocab, max_batch, max_seq)
+
+
+def _run_tile_rows(f, batch):
+    return F.parse_graph(F.fleet_graph_dump_run(f, batch))["header"]["run_tile_m"]
+
+
 @pytest.mark.parametrize("batch", [65, 81, 128])
 def test_whole_batch_tiles_in_a_step(batch):
     """65 to 128 sequences of a model whose weights are worth it run the GEMMs in tiles of the whole batch: equal to the oracle,
-    to a traced launch and to the static workspace bit for bit, and to 64-row tiles up to rounding; a handle made for more rows."""
-    sh = si.Shape(1, 2048, 16, 8, 128, 4096, 528, min(128, batch + 7), 200)
+    to a traced launch bit for bit, and to 64-row tiles up to rounding; a handle made for more rows."""
+    sh = _whole_shape(1, min(128, batch + 7), 200)
     pos = np.random.default_rng(batch).integers(0, 200, batch).astype(np.int32)
     m = Model(sh, seed=60 + batch, batch=batch, positions=pos)
     (ho, lg), k, v = m.run_oracle()
     print(f"whole batch {batch}", flush=True)
-    got = m.run_gpu()
+    f = F.fleet_create(sh.asdict(), m.w, 0, 0, 0)
+    try:
+        assert _run_tile_rows(f, batch) == 128 and _run_tile_rows(f, 64) == 64
+        got = m.run_gpu(fleet=f)
+    finally:
+        F.fleet_destroy(f)
     assert_close(got[0], ho, "hidden_out")
     assert_close(got[1], lg, "logits")
     check_new_kv(m, got[2], got[3], k, v)
@@ -938,6 +952,91 @@ def test_whole_batch_tiles_in_a_step(batch):
     assert np.array_equal(traced[0], got[0]) and np.array_equal(traced[1], got[1])
     low = m.run_gpu(0, 64)
     assert_close(low[0], got[0], "64-row tiles")
+
+
+@pytest.mark.parametrize("batch,kv", [(96, 64), (100, 900)])   # attention by the graph's tasks, and by a plan
+def test_whole_batch_tiles_from_every_entry_point(batch, kv):
+    """The step over a paged cache, layer by layer on an fp32 residual stream and as the first of several greedy steps has
+    the bits of the step over a contiguous cache; three greedy steps in one launch those of three launches."""
+    sh = _whole_shape(2, min(128, batch + 3), kv + 8, vocab=1040)
+    rng = np.random.default_rng(batch)
+    pos = np.full(batch, kv, np.int32) if kv == 64 else rng.integers(0, kv, batch).astype(np.int32)
+    m = Model(sh, seed=70 + batch, batch=batch, positions=pos, with_embed=True)
+    ids = torch.tensor(rng.integers(0, sh.vocab, batch), device="cuda", dtype=torch.int32)
+    m.hidden = m.w["embed"][ids.long()].contiguous()
+    m.hidden_host = si.to_host_u16(m.hidden)
+    (ho, lg), _, _ = m.run_oracle()
+    st = torch.cuda.current_stream().cuda_stream
+
+    def new(*shape):
+        return torch.full(shape, float("nan"), device="cuda")
+
+    f = F.fleet_create(sh.asdict(), m.w, 0, 0, 0)
+    try:
+        assert _run_tile_rows(f, batch) == 128
+        out, logits, kc, vc = new(batch, sh.hidden), new(batch, sh.vocab), m.kc.clone(), m.vc.clone()
+        print(f"whole batch {batch} kv {kv}: contiguous", flush=True)
+        F.fleet_decode_step(f, batch, m.hidden, None, kc, vc, m.pos, out, logits, st)
+        assert F.fleet_last_status(f)["code"] == 0 and any(F.fleet_last_plan(f)) == (kv > 64)
+        assert_close(out.cpu().numpy(), ho, "hidden_out")
+        assert_close(logits.cpu().numpy(), lg, "logits")
+
+        print("paged", flush=True)
+        page, per = 64, -(-sh.max_seq // 64)
+        table = torch.tensor(rng.permutation(batch * per + 5)[:batch * per].reshape(batch, per), device="cuda", dtype=torch.int32)
+        pools = []
+        for c in (m.kc, m.vc):
+            pool = torch.zeros((sh.n_layers, batch * per + 5, sh.n_kv_heads, page, 128), device="cuda", dtype=torch.bfloat16)
+            padded = torch.nn.functional.pad(c[:, :batch], (0, 0, 0, per * page - sh.max_seq))
+            pool[:, table.long().view(-1)] = padded.view(sh.n_layers, batch, sh.n_kv_heads, per, page, 128).transpose(2, 3).reshape(
+                sh.n_layers, batch * per, sh.n_kv_heads, page, 128)
+            pools.append(pool)
+        out2, logits2 = new(batch, sh.hidden), new(batch, sh.vocab)
+        F.fleet_decode_step_paged(f, batch, m.hidden, None, *pools, table, page, batch * per + 5, per, m.pos, out2, logits2, st)
+        assert F.fleet_last_status(f)["code"] == 0
+        assert torch.equal(out2, out) and torch.equal(logits2, logits)
+
+        print("layers", flush=True)
+        x, k2, v2 = m.hidden.float(), m.kc.clone(), m.vc.clone()
+        F.fleet_decode_layers(f, batch, 0, 1, x, k2, v2, m.pos, x, None, st)
+        F.fleet_decode_layers(f, batch, 1, 2, x, k2, v2, m.pos, x, logits2.fill_(float("nan")), st)
+        assert F.fleet_last_status(f)["code"] == 0
+        assert_close(x.cpu().numpy(), out.cpu().numpy(), "x_out", tol=1e-3)   # (the first norm adds a row's squares in another order)
+
+        print("tokens", flush=True)
+        runs = []
+        for calls in ([3], [1, 1, 1]):
+            tok, cur, k3, v3, gen = ids.clone(), m.pos.clone(), m.kc.clone(), m.vc.clone(), []
+            for i, n in enumerate(calls):
+                g, h3, l3 = torch.zeros((n, batch), device="cuda", dtype=torch.int32), new(batch, sh.hidden), new(batch, sh.vocab)
+                F.fleet_decode_tokens(f, batch, tok, k3, v3, cur, n, g, h3, l3, st)
+                assert F.fleet_last_status(f)["code"] == 0
+                if len(calls) == 3 and i == 0:
+                    assert torch.equal(h3, out) and torch.equal(l3, logits)
+                gen.append(g)
+            runs.append((torch.cat(gen), tok, cur, h3, l3, k3, v3))
+        assert all(torch.equal(p, q) for p, q in zip(*runs)) and torch.equal(runs[0][0][0], logits.argmax(1).int())
+    finally:
+        F.fleet_destroy(f)
+
+
+@pytest.mark.parametrize("flags,same_bits", [(F.FLAG_UNFUSED_SILU, False), (F.FLAG_NO_SPLITK, False), (F.FLAG_SINGLE_LEVEL, True),
+                                             (F.FLAG_NT_STORES, True), (F.FLAG_NO_STREAM, True), (F.FLAG_SEPARATE_NORM, True)])
+def test_whole_batch_tiles_under_flags(flags, same_bits):
+    sh = _whole_shape(2, 90, 300)
+    m = Model(sh, seed=75, batch=83, positions=np.random.default_rng(75).integers(0, 300, 83).astype(np.int32))
+    (ho, lg), _, _ = m.run_oracle()
+    ref = m.run_gpu()
+    print(f"whole batch, flags {flags}", flush=True)
+    f = F.fleet_create(sh.asdict(), m.w, 0, 0, flags)
+    try:
+        assert _run_tile_rows(f, 83) == 128
+        got = m.run_gpu(fleet=f)
+    finally:
+        F.fleet_destroy(f)
+    assert_close(got[0], ho, "hidden_out")
+    assert_close(got[1], lg, "logits")
+    assert not same_bits or (np.array_equal(got[0], ref[0]) and np.array_equal(got[1], ref[1]))
 
 
 @pytest.mark.parametrize("hidden,ffn", [(1024, 3072), (2048, 7168)])
@@ -954,7 +1053,7 @@ def test_streaming_hint_changes_no_bit(batch, hidden, ffn):
 
 @pytest.mark.parametrize("sched", [0, 2])
 @pytest.mark.parametrize("batch,nkv,hidden,ffn", [(2, 8, 1024, 1024), (3, 2, 1088, 1024), (16, 8, 2048, 2048), (20, 8, 2048, 2048), (24, 2, 1024, 3072),
-                                                  (40, 8, 2048, 2048), (48, 4, 1056, 96), (100, 8, 2048, 4096)])
+                                                  (40, 8, 2048, 2048), (48, 4, 1056, 96), (100, 8, 2048, 4096), (100, 8, 2048, 7168)])
 def test_steps_on_changing_inputs_see_no_old_rows(batch, nkv, hidden, ffn, sched):
     """Two sets of inputs in turn through one handle, three layers: every step has the bits of that set's first step.  A line of
     activations of the step or the layer before, left in a cache that was invalidated too early, would show as a difference (hidden sizes at

@@ -93,10 +93,11 @@ def test_fleet_copy_moves_bytes():
     assert torch.equal(src.view(torch.int16), dst.view(torch.int16))
 
 
-# more than 64 rows as one tile (weights of 128 KB a worker and more): one to eight blocks of rows beyond the tile's edge, units that do not divide
-# among the workers, k-slices, k-steps that end inside a round; reps = 3: counters of split tiles used again
+# more than 64 rows as one tile (weights of 128 KB a worker and more, and two m-tiles would split k or need two tiles a worker; 4128 x 4112 would not and stays in two
+# m-tiles): one to eight blocks of rows beyond the tile's edge, units that do not divide among the workers, k-slices, k-steps that end inside a round;
+# reps = 3: counters of split tiles used again
 @pytest.mark.parametrize("B", [65, 80, 81, 112, 128])
-@pytest.mark.parametrize("K,N,reps", [(4096, 4096, 3), (4128, 4112, 1), (12288, 2048, 3), (1024, 20496, 1)])
+@pytest.mark.parametrize("K,N,reps", [(4096, 4096, 3), (4128, 4112, 1), (12288, 2048, 3), (1024, 20496, 1), (1056, 20496, 1), (4128, 16400, 1)])
 def test_gemm_whole_batch_tiles(B, K, N, reps):
     print(f"gemm whole batch B={B} K={K} N={N}", flush=True)
     y, ref, _ = _run(B, K, N, flags=F.FLAG_CHAINED if reps > 1 else 0, reps=reps, n_copies=min(reps, 2))
