@@ -234,7 +234,7 @@ int fleet_decode_step_static(fleet_t *f, int32_t batch, const void *hidden_in, c
  *   page_size  a power of two >= 64; positions[b] < table_stride * page_size and < max_seq
  * Everything else as in fleet_decode_step.  A page index outside [0, n_pages) or a position
  * beyond the table ends the step with FLEET_EINVAL in the status; nothing is read or
- * written through such an entry.
+ * written through such an entry.  Entries behind the page of positions[b] are not looked at.
  */
 int fleet_decode_step_paged(fleet_t *f, int32_t batch, const void *hidden_in, const int32_t *tokens,
                             void *k_pool, void *v_pool, const int32_t *page_table,

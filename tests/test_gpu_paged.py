@@ -87,3 +87,33 @@ def test_bad_page_index_is_reported():
     F.fleet_destroy(f)
     print("status:", st, flush=True)
     assert st["code"] == -1
+
+
+@pytest.mark.parametrize("batch,kv,page_size", [(1, 1025, 64), (2, 2053, 64), (2, 2053, 256), (5, 1100, 128), (12, 450, 64), (20, 300, 64), (40, 300, 64)])
+def test_page_tables_that_end_with_the_sequence(batch, kv, page_size):
+    """Attention splits are multiples of 64 keys, so the last ones may lie behind a sequence's end.  A table that has
+    no column for them, or an invalid entry (sequences shorter than the table), is right all the same: the step
+    equals the one over a contiguous cache."""
+    sh = si.reduced_shape(max_batch=batch, max_seq=kv + 1, n_layers=2, vocab=0)
+    pos = np.random.default_rng(batch).integers(0, kv + 1, batch).astype(np.int32)
+    pos[0] = kv                                     # the table has no column to spare for this one
+    m = Model(sh, seed=90 + batch, batch=batch, positions=pos)
+    per_seq = -(-(kv + 1) // page_size)
+    n_pages = batch * per_seq
+    table = np.random.default_rng(7).permutation(n_pages).reshape(batch, per_seq).astype(np.int32)
+    kp, vp = _to_pool(m.kc, table, page_size, n_pages), _to_pool(m.vc, table, page_size, n_pages)
+    for b in range(batch):
+        table[b, pos[b] // page_size + 1:] = (-1, n_pages, 1 << 30)[b % 3]
+    print(f"tight page table batch={batch} kv={kv} page_size={page_size}", flush=True)
+    hout = torch.full((batch, sh.hidden), float("nan"), device="cuda", dtype=torch.float32)
+    ref = torch.full_like(hout, float("nan"))
+    f = F.fleet_create(sh.asdict(), m.w, 0, 0, 0)
+    try:
+        F.fleet_decode_step(f, batch, m.hidden, None, m.kc.clone(), m.vc.clone(), m.pos, ref, None)
+        assert F.fleet_last_status(f)["code"] == 0
+        F.fleet_decode_step_paged(f, batch, m.hidden, None, kp, vp, torch.tensor(table, device="cuda"), page_size, n_pages, per_seq, m.pos, hout, None)
+        st = F.fleet_last_status(f)
+        assert st["code"] == 0, st
+    finally:
+        F.fleet_destroy(f)
+    assert_close(hout.cpu().numpy(), ref.cpu().numpy(), "hidden_out")
