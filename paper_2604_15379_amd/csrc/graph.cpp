@@ -576,7 +576,7 @@ static bool early_invalidate(const std::set<std::pair<int, int>>& gemm_reads, co
   const auto read = gemm_reads.lower_bound({in, prev_stage});
   if (read != gemm_reads.end() && read->first == in && read->second < stage) return false;
   switch (in) {
-    case BUF_N: return norm_by_blocks(op[O_K], op[O_BATCH]);
+    case BUF_N: return norm_by_blocks(op[O_K], op[O_BATCH], op[O_WKIND] == W_LM);
     case BUF_X: return op[O_K] % (32 * info.n_xcd) == 0;
     case BUF_ATT: return info.n_kv_heads % info.n_xcd == 0;
     case BUF_H: return !(info.flags & FLEET_FLAG_UNFUSED_SILU);

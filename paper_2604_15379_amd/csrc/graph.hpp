@@ -126,10 +126,11 @@ int mfma_blocks(int tile_m);
 constexpr int WHOLE_BLOCKS = 8;     // the same of the kernel for tiles of the whole batch
 // Are the norm stages of a graph's MFMA kernels done by operand blocks (body_rmsnorm_blocks)?  Sums of squares are read four at
 // a time.  Rows of 1024 features are short enough for a task per row: its sum is one more trip through LDS, and a block's tasks
-// share a few wavefronts.  Two layers of that size, by rows and by blocks: batch 65 to 128 134.6 and 136.2 us, 140.9 and 142.2; greedy tokens (final norm) at
-// batch 2, 3 and 8, eight steps, 711 and 724, 723 and 732, 750 and 755; but at 17 to 64 rows, where blocks let the GEMM behind them invalidate
-// early, batch 24 101.8 and 99.6, batch 64 132.3 and 130.9.  With 2048 features blocks are ahead everywhere (batch 24 129.7 and 126.7, batch 96 235.7 and 233.8).
-constexpr bool norm_by_blocks(int hidden, int batch) { return hidden % 64 == 0 && (hidden >= 2048 || (batch > 16 && batch <= 64)); }
+// share a few wavefronts.  Two layers of that size, by rows and by blocks: batch 65 to 128 134.6 and 136.2 us, 140.9 and 142.2; but in the layers of
+// 17 to 64 rows, where blocks let the GEMM behind them invalidate early, batch 24 101.8 and 99.6, batch 64 132.3 and 130.9.  The final norm: eight
+// greedy tokens at batch 2, 3 and 8 711 and 724, 723 and 732, 750 and 755, at batch 24 and 48 905 and 914, 1122 and 1128; one layer and a head at batch 24
+// 64.5 and 66.2.  With 2048 features blocks are ahead everywhere (batch 24 129.7 and 126.7, batch 96 235.7 and 233.8).
+constexpr bool norm_by_blocks(int hidden, int batch, bool final_norm) { return hidden % 64 == 0 && (hidden >= 2048 || (!final_norm && batch > 16 && batch <= 64)); }
 // largest batch that runs the FMA GEMV kernels (larger batches run the MFMA kernels): 1, or
 // what the environment variable FLEET_FMA_MAX_BATCH (0..8) says.  Read once by whoever owns
 // a set of graphs (fleet_create, fleet_gemm, fleet_graph_build) and handed to the builders, so
