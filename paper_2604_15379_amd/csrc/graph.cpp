@@ -533,10 +533,11 @@ int64_t gpart_bytes(const Graph& g) {
 //   * otherwise whole tiles: hidden 2048, FFN 7168 (224 KB; 38 tiles for 32 workers) 217 and 203, 263 and 252; hidden 2560, FFN 7168 242 and 202, 275 and 244; one 8B layer at batch 100 /
 //     KV 100-1000 222 and 193; a 12288 x 4096 GEMM at batch 96 34.3 and 32.1, 4096 x 4096 (128 KB) 18.2 and 16.9, 1024 x 16384 20.8 and 15.3;
 //   * below 128 KB a worker the split sums cost more than the weights: hidden 1024, FFN 3072 (48 KB) at batch 128 132 and 153.
-// An explicit height and the other schedules (whose tasks name an m-tile) keep the 64-row tiles.
+// An explicit height and the other schedules (whose tasks name an m-tile) keep the 64-row tiles, and so does a handle that may not split k: the down projection
+// of whole tiles then has one unit a tile (two 8B layers at batch 96 / KV 512 without split k 400 us in two m-tiles, 436 in whole tiles).
 static bool takes_whole_batch(const Graph& g, const RunInfo& info) {
   const int32_t* h = g.header.data();
-  if (h[H_PATH] != P_MFMA || h[H_SCHED] != FLEET_SCHED_COOPERATIVE || info.tile_m != 0 || h[H_M_TILES] < 2) return false;
+  if ((info.flags & FLEET_FLAG_NO_SPLITK) || h[H_PATH] != P_MFMA || h[H_SCHED] != FLEET_SCHED_COOPERATIVE || info.tile_m != 0 || h[H_M_TILES] < 2) return false;
   const int32_t* top = nullptr;
   int64_t most = 0;
   for (int i = 0; i < g.n_ops(); ++i) {
@@ -554,7 +555,7 @@ static bool takes_whole_batch(const Graph& g, const RunInfo& info) {
 static void widen_op(int32_t* o, const RunInfo& info) {
   if (o[O_BODY] != B_GEMM) return;
   const int nb = o[O_EPI] == E_SWIGLU_BF16 ? 2 : 1, mtb = (o[O_BATCH] + 15) / 16, ks = (o[O_AUX2] >> 16) & 15;
-  const bool split = !(info.flags & FLEET_FLAG_NO_SPLITK) && o[O_N_UNITS] <= GEMM_TILE_COUNTERS && (info.step || ks > 1);
+  const bool split = o[O_N_UNITS] <= GEMM_TILE_COUNTERS && (info.step || ks > 1);
   const MfmaPlan pl = plan_wide((o[O_N_UNITS] + info.n_xcd - 1) / info.n_xcd, info.n_workers / info.n_xcd, o[O_K], nb, mtb, split, nb * WHOLE_BLOCKS, info.part_bytes / 1024);
   o[O_AUX2] = (o[O_AUX2] & ~((15 << 12) | (15 << 16) | (1 << 21))) | (pl.G << 12) | (pl.KS << 16);
   o[O_M_TILES] = 1;

@@ -498,10 +498,11 @@ def test_which_steps_run_whole_batch_tiles(hidden, ffn, whole):
         assert rows(batch) == (128 if whole else 64)
         assert rows(batch, 1) == rows(batch, 2) == rows(batch, 0, 64) == 64
         assert rows(batch, 0, 32) == 32 and rows(batch, 0, 0, 64) == rows(batch)   # (64: no streaming hint)
+        assert rows(batch, 0, 0, 32) == 64                                         # (32: no split of k)
     assert rows(64) == 64 and rows(33) == 48 and rows(8) == 16
 
 
-@pytest.mark.parametrize("flags", [0, 32, 256])
+@pytest.mark.parametrize("flags", [0, 128, 256])
 @pytest.mark.parametrize("batch", [65, 81, 100, 128])
 def test_plans_of_whole_batch_tiles(batch, flags):
     """One m-tile of 128 rows, no more row blocks than a tile has registers for, whole k-steps per
@@ -522,7 +523,7 @@ def test_plans_of_whole_batch_tiles(batch, flags):
             assert op[8] == 1 and op[9] == 128 and not op[15] >> 21 & 1
             assert 1 <= G * nb <= 6 and KS in (1, 2, 4, 8)
             if KS > 1:
-                assert not flags & 32 and op[4] % (128 * KS) == 0 and op[7] <= 4096
+                assert op[4] % (128 * KS) == 0 and op[7] <= 4096
                 assert KS * nb * -(-int(op[7]) // 8) * 8 * 1024 <= region    # an XCD's units, 8 blocks of 1 KB each
 
 

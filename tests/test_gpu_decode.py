@@ -1020,7 +1020,7 @@ def test_whole_batch_tiles_from_every_entry_point(batch, kv):
         F.fleet_destroy(f)
 
 
-@pytest.mark.parametrize("flags,same_bits", [(F.FLAG_UNFUSED_SILU, False), (F.FLAG_NO_SPLITK, False), (F.FLAG_SINGLE_LEVEL, True),
+@pytest.mark.parametrize("flags,same_bits", [(F.FLAG_UNFUSED_SILU, False), (F.FLAG_NO_RESIDENT, True), (F.FLAG_SINGLE_LEVEL, True),
                                              (F.FLAG_NT_STORES, True), (F.FLAG_NO_STREAM, True), (F.FLAG_SEPARATE_NORM, True)])
 def test_whole_batch_tiles_under_flags(flags, same_bits):
     sh = _whole_shape(2, 90, 300)
