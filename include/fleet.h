@@ -91,7 +91,9 @@ typedef struct {
   int32_t sched_mode; /* enum fleet_sched                                                */
   int32_t tile_m;     /* GEMM tile height along the batch on the MFMA path: 16, 32, 64, or
                          0 = whole batch rounded up to 16 (reads each weight once).
-                         Batches above 64 use 64-row tiles (0) or the given height.
+                         Batches above 64 use the given height, or (0) 64-row tiles; with 0 and
+                         the cooperative schedule one tile of the whole batch where the weights
+                         are worth it (fleet_graph_dump_run: header word 16).
                          Batch 1 runs FMA GEMV kernels, larger batches bf16 MFMA
                          kernels; the environment variable FLEET_FMA_MAX_BATCH (0..8),
                          read once by fleet_create (and by fleet_gemm and
@@ -178,7 +180,8 @@ int fleet_create(const fleet_shape_t *shape, const fleet_weights_t *weights, fle
  * fleet_last_status() reports FLEET_ETIMEOUT.
  * The result is a function of the inputs alone: every reduction has a fixed order, so
  * repeating the step on the same inputs gives the same bits (for a given batch size,
- * schedule and tile height).  The positions are inputs too: with 32- and 64-row tiles (from 17
+ * schedule and tile height; above 64 rows and with tile_m 0 the cooperative and the unaware schedule may run
+ * different tiles, and then differ in last bits).  The positions are inputs too: with 32- and 64-row tiles (from 17
  * sequences on) the XCD-aware schedules deal the keys of the step to the workers by the lengths of
  * all its sequences, so the order in which one sequence's keys are added up, and with it the last
  * bits of its row, may change with the lengths of the others.

@@ -237,7 +237,8 @@ MfmaPlan plan_mfma(int ux, int wpx, int K, int nb, int mt_blocks, int m_tiles, b
 }
 
 // A worker takes in 45 KB/us, weights and activations together (700 KB/us of weights per XCD at most); a tile costs 1.5 us on
-// top, a split-K tile 3.5 us and the last arriver's reading of all slices at 60 KB/us.
+// top, a split-K tile 3.5 us and the reading of all its slices at 60 KB/us.  (Fitted with one worker reading them all; a tile's workers share that now,
+// a KS-th each behind a wait for all of them.  Cost per slice at 1.5 or 7 us instead of 3.5: the same plans.)
 MfmaPlan plan_wide(int ux, int wpx, int K, int nb, int mtb, bool allow_split, int64_t part_kb, int64_t max_part_kb) {
   const int gmax = 6 / nb;
   ux = std::max(1, ux); wpx = std::max(1, wpx);
