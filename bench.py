@@ -27,23 +27,23 @@ HBM_PEAK_GBPS = 8000.0
 # same counters read for a plain copy of known size.  Key: (batch, kv, kv_min, sched, tile_m, flags)
 # at 36 layers and seed 2; any other workload reports null unless --traffic-bytes is given.
 MEASURED_TRAFFIC = {
-    (1, 1024, 0, 0, 0, 0): 15422163616,
-    (1, 1024, 0, 1, 0, 0): 15414246272,
-    (1, 1024, 0, 0, 0, 64): 16196907856,
-    (1, 1024, 0, 0, 0, 256): 16248064144,
-    (8, 2048, 1024, 0, 0, 0): 17325551872,
-    (8, 2048, 1024, 0, 0, 4): 17343859520,
-    (8, 2048, 1024, 1, 0, 0): 17483153184,
-    (32, 2048, 1024, 0, 0, 0): 23610664256,
-    (32, 2048, 1024, 0, 16, 0): 24139679936,
-    (32, 2048, 1024, 1, 16, 0): 32707753984,
-    (32, 2048, 1024, 2, 16, 0): 38603898944,
-    (64, 4096, 0, 0, 0, 0): 55954839808,
-    (64, 4096, 0, 0, 16, 0): 57061564928,
-    (64, 4096, 0, 1, 16, 0): 81736576064,
-    (64, 4096, 0, 2, 16, 0): 100458856000,
-    (64, 4096, 0, 0, 16, 32): 56751606528,
-    (64, 4096, 0, 0, 16, 2048): 57065017984,
+    (1, 1024, 0, 0, 0, 0): 15428159648,
+    (1, 1024, 0, 1, 0, 0): 15415941376,
+    (1, 1024, 0, 0, 0, 64): 16192346688,
+    (1, 1024, 0, 0, 0, 256): 16249654800,
+    (8, 2048, 1024, 0, 0, 0): 17326339328,
+    (8, 2048, 1024, 0, 0, 4): 17370199424,
+    (8, 2048, 1024, 1, 0, 0): 17485056096,
+    (32, 2048, 1024, 0, 0, 0): 23550634688,
+    (32, 2048, 1024, 0, 16, 0): 24143511488,
+    (32, 2048, 1024, 1, 16, 0): 32717955712,
+    (32, 2048, 1024, 2, 16, 0): 38603282304,
+    (64, 4096, 0, 0, 0, 0): 55852308864,
+    (64, 4096, 0, 0, 16, 0): 57057698560,
+    (64, 4096, 0, 1, 16, 0): 81737027008,
+    (64, 4096, 0, 2, 16, 0): 100445016576,
+    (64, 4096, 0, 0, 16, 32): 56749400000,
+    (64, 4096, 0, 0, 16, 2048): 57055370112,
 }
 
 
