@@ -561,8 +561,9 @@ int run_layers(fleet* f, const StepArgs& a, hipStream_t st) {
   P.direct_in = a.with_ingest && !P.trace &&
                 (op1[O_BODY] == B_RMSNORM || (op1[O_BODY] == B_GEMM && op1[O_PATH] == P_FMA && ((op1[O_AUX2] >> 8) & 3) == X_LDS_NORM));
   P.embed = f->embed;
-  P.norm_blocks = norm_by_blocks(f->shape.hidden, g.header[H_BATCH], false, f->shape.sched_mode);
-  P.final_blocks = norm_by_blocks(f->shape.hidden, g.header[H_BATCH], true, f->shape.sched_mode);
+  P.norm_blocks = norm_by_blocks(f->shape.hidden, g.header[H_BATCH], false);
+  P.layer_blocks = P.norm_blocks && !norm_by_rows(f->shape.hidden, f->shape.sched_mode);
+  P.final_blocks = norm_by_blocks(f->shape.hidden, g.header[H_BATCH], true);
   const int mb = a.with_ingest && !P.direct_in ? 0 : 1 + a.layer_begin;
   const int me = !final_stage ? 1 + a.layer_end : (a.logits ? L + 3 : L + 2);
   P.direct_out = final_stage ? 0 : a.layer_end;

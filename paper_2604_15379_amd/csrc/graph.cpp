@@ -572,13 +572,13 @@ static void widen_op(int32_t* o, const RunInfo& info) {
 //     unit's tile all of its 16 features), of the norm by operand blocks, of the attention output where a kv head's sequences share an XCD (8 rows by 8
 //     features of one head), and of the fp32 residual rows where every XCD's units of 64 bytes a row begin on a line.
 // (gemm_reads: (buffer, stage) of every GEMM task's input)
-static bool early_invalidate(const std::set<std::pair<int, int>>& gemm_reads, const int32_t* op, int stage, int prev_stage, int sched, const RunInfo& info) {
+static bool early_invalidate(const std::set<std::pair<int, int>>& gemm_reads, const int32_t* op, int stage, int prev_stage, const RunInfo& info) {
   const int in = op[O_IN_BUF];
   if (op[O_PATH] != P_MFMA) return false;
   const auto read = gemm_reads.lower_bound({in, prev_stage});
   if (read != gemm_reads.end() && read->first == in && read->second < stage) return false;
   switch (in) {
-    case BUF_N: return norm_by_blocks(op[O_K], op[O_BATCH], op[O_WKIND] == W_LM, sched);
+    case BUF_N: return norm_by_blocks(op[O_K], op[O_BATCH], op[O_WKIND] == W_LM);
     case BUF_X: return op[O_K] % (32 * info.n_xcd) == 0;
     case BUF_ATT: return info.n_kv_heads % info.n_xcd == 0;
     case BUF_H: return !(info.flags & FLEET_FLAG_UNFUSED_SILU);
@@ -629,7 +629,7 @@ Graph run_graph(const Graph& g, const RunInfo& info) {
       const int32_t* e = &r.qents[(size_t)qi * QENT_WORDS];
       if (e[Q_DIST] != D_CHIPLET) continue;
       int32_t* tw = task(e[Q_FIRST]);
-      if (early_invalidate(gemm_reads, op_of(e[Q_FIRST]), tw[T_STAGE], prev_stage, g.header[H_SCHED], info)) tw[T_HINTS] |= HINT_INV;
+      if (early_invalidate(gemm_reads, op_of(e[Q_FIRST]), tw[T_STAGE], prev_stage, info)) tw[T_HINTS] |= HINT_INV;
       prev_stage = tw[T_STAGE];
     }
   }

@@ -129,8 +129,11 @@ constexpr int WHOLE_BLOCKS = 8;     // the same of the kernel for tiles of the w
 // share a few wavefronts.  Two layers of that size, by rows and by blocks: batch 65 to 128 134.6 and 136.2 us, 140.9 and 142.2; but in the layers of
 // 17 to 64 rows, where blocks let the GEMM behind them invalidate early, batch 24 101.8 and 99.6, batch 64 132.3 and 130.9.  The final norm: eight
 // greedy tokens at batch 2, 3 and 8 711 and 724, 723 and 732, 750 and 755, at batch 24 and 48 905 and 914, 1122 and 1128; one layer and a head at batch 24
-// 64.5 and 66.2; nor does a GEMM of the chiplet-unaware schedule invalidate early (batch 24 98.1 and 101.2).  With 2048 features blocks are ahead everywhere (batch 24 129.7 and 126.7, batch 96 235.7 and 233.8).
-constexpr bool norm_by_blocks(int hidden, int batch, bool final_norm, int sched) { return hidden % 64 == 0 && (hidden >= 2048 || (!final_norm && sched != FLEET_SCHED_UNAWARE && batch > 16 && batch <= 64)); }
+// 64.5 and 66.2.  With 2048 features blocks are ahead everywhere (batch 24 129.7 and 126.7, batch 96 235.7 and 233.8).
+constexpr bool norm_by_blocks(int hidden, int batch, bool final_norm) { return hidden % 64 == 0 && (hidden >= 2048 || (!final_norm && batch > 16 && batch <= 64)); }
+// A GEMM of the chiplet-unaware schedule does not invalidate early: its layers' norms of short rows take a task per row there too (by rows and by blocks:
+// batch 24 98.1 and 101.2), with the sums that blocks would take, so that the schedules have the same bits.
+constexpr bool norm_by_rows(int hidden, int sched) { return hidden < 2048 && sched == FLEET_SCHED_UNAWARE; }
 // largest batch that runs the FMA GEMV kernels (larger batches run the MFMA kernels): 1, or
 // what the environment variable FLEET_FMA_MAX_BATCH (0..8) says.  Read once by whoever owns
 // a set of graphs (fleet_create, fleet_gemm, fleet_graph_build) and handed to the builders, so

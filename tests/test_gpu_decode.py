@@ -537,6 +537,21 @@ def test_input_rows_from_token_ids_and_hidden_states(batch, hidden):
         assert step(0, None, tok, True)[0] == -1
 
 
+@pytest.mark.parametrize("flags", [0, F.FLAG_SEPARATE_NORM])
+@pytest.mark.parametrize("batch,tile_m", [(17, 0), (20, 16), (32, 0), (33, 0), (40, 32), (64, 0), (64, 16)])
+def test_short_rows_have_the_same_bits_in_both_schedules(batch, tile_m, flags):
+    """Norms of 1024 features: tasks of operand blocks in the cooperative schedule, a row per task in the chiplet-unaware one,
+    whose sums are added up in the same order; equal lengths (attention without a plan)."""
+    sh = si.reduced_shape(max_batch=batch, max_seq=96, n_layers=2, vocab=1024)
+    m = Model(sh, seed=61, batch=batch, positions=np.full(batch, 80, np.int32))
+    outs = []
+    for sched in (F.SCHED_COOPERATIVE, F.SCHED_UNAWARE):
+        print(f"both schedules batch={batch} tile_m={tile_m} flags={flags} sched={sched}", flush=True)
+        outs.append(m.run_gpu(sched, tile_m, flags)[:4])
+    for a, b in zip(*outs):
+        assert np.array_equal(a, b)
+
+
 @pytest.mark.parametrize("ffn", [32, 64, 96, 128])
 @pytest.mark.parametrize("batch,fma_max", [(1, 1), (2, 8), (7, 8), (2, 1), (16, 1), (20, 1), (40, 1)])
 def test_ffn_with_fewer_units_than_xcds(monkeypatch, batch, fma_max, ffn):
