@@ -446,6 +446,8 @@ int upload_graph(DevGraph* dg, const fleet* f, const void* const* gemm_copies, c
     memcpy(d + dev::FAT_W, &w[tw[T_OP]], sizeof(void*));
     memcpy(d + dev::FAT_W2, &w2[tw[T_OP]], sizeof(void*));
     d[dev::FAT_ID] = t;
+    if (tw[T_WAIT_EVENT] >= 0) d[dev::T_WAIT_NEED] = g.events[(size_t)tw[T_WAIT_EVENT] * EVENT_WORDS + E_THRESHOLD];
+    if (tw[T_SIGNAL_EVENT] >= 0) d[dev::T_SIG_KIND] = g.events[(size_t)tw[T_SIGNAL_EVENT] * EVENT_WORDS + E_KIND];
   }
   // CU-tasks dealt inside one XCD: how many of them signal the task's event from that XCD
   for (int x = 0; x < n_xcd; ++x)
