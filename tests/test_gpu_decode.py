@@ -326,6 +326,57 @@ def test_pairs_laid_end_to_end_where_an_xcd_has_workers_to_spare(batch, max_batc
     assert np.array_equal(traced[0], got[0])
 
 
+@pytest.mark.parametrize("nq,nkv,batch,lengths", [(8, 8, 100, "mixed"), (16, 8, 128, "short"), (6, 2, 65, "mixed"), (32, 8, 97, "equal"), (8, 8, 128, "few long"), (8, 8, 128, "many long"), (4, 1, 70, "short")])
+def test_attention_beside_tiles_of_the_whole_batch(nq, nkv, batch, lengths):
+    """65 to 128 rows of a model that runs tiles of the whole batch: every wavefront walks keys of its own over the ends of pairs.  Lengths at the edges of octs, of
+    a wavefront's part and of a worker's piece (empty and single-key caches, pairs inside one wavefront, over several, over several workers, more pairs in
+    a piece than a worker has room for), contiguous and paged; equal to the oracle, a traced launch and a second one bit for bit."""
+    sh = si.Shape(1, 1024, nq, nkv, 128, 9216, 0, batch, 1100)
+    rng = np.random.default_rng(batch + nkv)
+    pos = {"mixed": rng.integers(0, 700, batch), "short": rng.integers(0, 40, batch), "equal": np.full(batch, 333), "few long": rng.integers(0, 9, batch), "many long": rng.integers(0, 9, batch)}[lengths].astype(np.int32)
+    if lengths != "equal":
+        edges = [0, 1, 7, 8, 9, 31, 32, 33, 63, 64, 65, 255, 256, 257] if lengths == "mixed" else [0, 1, 7, 8, 9, 1, 0]
+        pos[5:5 + len(edges)] = edges
+    if lengths.endswith("long"):
+        pos[:4 if lengths == "few long" else 12] = 1099 - rng.integers(0, 9)
+    m = Model(sh, seed=41 + nkv, batch=batch, positions=pos)
+    m.w["wo"][0].mul_(100.0)
+    m.w_host = si.weights_to_host(m.w)
+    (ho, _), k, v = m.run_oracle()
+    print(f"whole tiles: nq {nq} nkv {nkv} batch {batch} {lengths}", flush=True)
+    f = F.fleet_create(sh.asdict(), m.w, 0, 0, 0)
+    try:
+        assert F.parse_graph(F.fleet_graph_dump_run(f, batch))["header"]["run_tile_m"] == 128
+        got = m.run_gpu(fleet=f)
+        assert F.fleet_last_plan(f)[0] == {"equal": END_TO_END, "many long": 0}.get(lengths, F.fleet_last_plan(f)[0])
+        assert_close(got[0], ho, "hidden_out")
+        check_new_kv(m, got[2], got[3], k, v)
+        assert np.array_equal(m.run_gpu(fleet=f)[0], got[0])
+        per = 18
+        table = torch.randperm(per * batch, generator=torch.Generator().manual_seed(batch)).to(torch.int32).view(batch, per)
+        kc, vc = _pools(m.kc, m.vc, batch, 64, table)
+        hout = torch.full((batch, sh.hidden), float("nan"), device="cuda", dtype=torch.float32)
+        print("  paged", flush=True)
+        F.fleet_decode_step_paged(f, batch, m.hidden, None, kc, vc, table.cuda(), 64, per * batch, per, m.pos, hout, None)
+        assert F.fleet_last_status(f)["code"] == 0
+        assert_close(hout.cpu().numpy(), ho, "hidden_out, paged")
+        for row, kind in ((0, "position"), (batch // 2, "position"), (5, "page"), (batch - 1, "page")):   # reported, and the next step is right
+            bad_pos, bad_table = m.pos.clone(), table.clone()
+            if kind == "position":
+                bad_pos[row] = sh.max_seq
+            else:
+                bad_table[row, pos[row] // 64] = per * batch
+            F.fleet_decode_step_paged(f, batch, m.hidden, None, kc, vc, bad_table.cuda(), 64, per * batch, per, bad_pos, hout, None)
+            assert F.fleet_last_status(f)["code"] == -1, (row, kind)
+        F.fleet_decode_step_paged(f, batch, m.hidden, None, kc, vc, table.cuda(), 64, per * batch, per, m.pos, hout, None)
+        assert F.fleet_last_status(f)["code"] == 0
+        assert_close(hout.cpu().numpy(), ho, "hidden_out, paged, after bad ones")
+    finally:
+        F.fleet_destroy(f)
+    traced = m.run_gpu(0, 0, F.FLAG_TRACE)
+    assert np.array_equal(traced[0], got[0])
+
+
 @pytest.mark.parametrize("batch,max_batch,form", [(20, 32, WHOLE), (64, 64, END_TO_END)])
 def test_bad_positions_and_pages_under_a_plan(batch, max_batch, form):
     """A position outside the cache, a page outside the pool and a table that is too short end a step that runs by plan as they end any
