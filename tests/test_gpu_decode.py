@@ -640,6 +640,28 @@ def test_hidden_sizes_above_4096(batch, hidden):
     assert_close(got[1], lg, "logits")
 
 
+# k-rounds of 256: one of 64 features; two, the last ragged; three; four (a whole ring); five, the last of 64; ten, the last of 64; units an XCD that
+# are and are not a whole number of tiles (64 to 4096 rows of gate, 4 to 148 units of O and down)
+@pytest.mark.parametrize("hidden,ffn,nq", [(64, 160, 4), (320, 544, 4), (768, 800, 4), (1024, 3072, 16), (1088, 1056, 4), (2368, 4096, 8)])
+@pytest.mark.parametrize("batch", [2, 15, 16])
+def test_small_tiles_request_what_they_have(hidden, ffn, nq, batch):
+    """16-row tiles of small models: gate/up with one unit a tile, QKV, O and down register-resident with one or two units; k-rounds and
+    units that a tile does not have are not requested.  A step has the oracle's results, and twice the same bits."""
+    sh = si.Shape(2, hidden, nq, nq // 4, 128, ffn, 528, batch, 90)
+    g = F.parse_graph(F.fleet_graph_build_run(sh.asdict(), batch, 8, 256, 0, 0, 0))
+    gemms = [op for op in g["ops"] if op[0] == 2 and op[1] == 0]
+    assert [(int(op[13]), int(op[15]) >> 12 & 15, int(op[15]) >> 21 & 1) for op in gemms[:4]] == [(1, 1, 1), (2, 1, 1), (3, 1, 0), (4, 1, 1)]
+    m = Model(sh, seed=140 + batch, batch=batch, positions=np.random.default_rng(hidden).integers(0, 90, batch).astype(np.int32))
+    print(f"hidden {hidden} ffn {ffn} batch {batch}", flush=True)
+    (ho, lg), k, v = m.run_oracle()
+    got = m.run_gpu()
+    assert_close(got[0], ho, "hidden_out")
+    assert_close(got[1], lg, "logits")
+    check_new_kv(m, got[2], got[3], k, v)
+    again = m.run_gpu()
+    assert all(np.array_equal(x, y) for x, y in zip(got[:2], again[:2]))
+
+
 def test_misaligned_buffers_are_rejected():
     """Outputs are written in 16-byte pieces: a logits or hidden_out pointer that is not
     16-byte aligned is refused on the host before anything is launched."""
