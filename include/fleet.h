@@ -333,7 +333,8 @@ int fleet_last_status(fleet_t *f, fleet_status_t *out);
 /*
  * fleet_last_plan (test / measurement): synchronise the device and store into form[0..7] (HOST) how the keys of each
  * XCD's attention stage were dealt to its workers in the last step: 0 by the graph (one task per sequence, kv
- * head and split), 1 whole workers per (sequence, kv head) pair, 2 the pairs end to end in equal pieces.
+ * head and split, or in tiles of the whole batch as many whole pairs per worker), 1 whole workers per (sequence, kv head)
+ * pair, 2 the pairs end to end in equal pieces.
  */
 int fleet_last_plan(fleet_t *f, int32_t *form);
 

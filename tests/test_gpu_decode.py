@@ -377,6 +377,52 @@ def test_attention_beside_tiles_of_the_whole_batch(nq, nkv, batch, lengths):
     assert np.array_equal(traced[0], got[0])
 
 
+@pytest.mark.parametrize("paged", [False, True])
+def test_infinities_and_nans_beside_tiles_of_the_whole_batch(paged):
+    """As test_infinities_and_nans_in_the_cache_stay_with_their_sequence, where a wavefront walks the keys of several sequences: beyond the
+    lengths anything may lie; inside one, a row becomes not a number and the others keep their bits."""
+    batch, cap = 100, 300
+    sh = si.Shape(1, 1024, 8, 8, 128, 9216, 0, batch, cap)
+    rng = np.random.default_rng(3)
+    pos = rng.integers(0, cap - 1, batch).astype(np.int32)
+    pos[:9] = [0, 1, 7, 8, 9, 63, 64, 65, cap - 1]
+    m = Model(sh, seed=43, batch=batch, positions=pos)
+    table = torch.randperm(5 * batch, generator=torch.Generator().manual_seed(1)).to(torch.int32).view(batch, 5)
+    f = F.fleet_create(sh.asdict(), m.w, 0, 0, 0)
+
+    def step(kc, vc):
+        out = torch.full((batch, sh.hidden), 7.0, device="cuda", dtype=torch.float32)
+        if paged:
+            kp, vp = _pools(kc, vc, batch, 64, table)
+            F.fleet_decode_step_paged(f, batch, m.hidden, None, kp, vp, table.cuda(), 64, 5 * batch, 5, m.pos, out, None)
+        else:
+            F.fleet_decode_step(f, batch, m.hidden, None, kc, vc, m.pos, out, None)
+        assert F.fleet_last_status(f)["code"] == 0
+        return out
+
+    try:
+        assert F.parse_graph(F.fleet_graph_dump_run(f, batch))["header"]["run_tile_m"] == 128
+        ref = step(m.kc.clone(), m.vc.clone())
+        assert F.fleet_last_plan(f)[0] == END_TO_END and torch.isfinite(ref).all()
+        beyond = torch.arange(cap, device="cuda")[None, :] >= m.pos[:, None]
+        for bad in (float("nan"), float("inf")):
+            print(f"whole tiles, paged {paged}: {bad} beyond the lengths", flush=True)
+            kc, vc = m.kc.clone(), m.vc.clone()
+            for t in (kc, vc):
+                t[:, :batch].masked_fill_(beyond[None, :, None, :, None], bad)
+            assert torch.equal(step(kc, vc), ref)
+        for row, slot in ((8, 100), (int(pos[9:].argmax()) + 9, int(pos[9:].max()) - 1), (2, 0)):
+            others = [b for b in range(batch) if b != row]
+            for what in ("k", "v"):
+                print(f"whole tiles, paged {paged}: nan in a {what} of sequence {row}", flush=True)
+                kc, vc = m.kc.clone(), m.vc.clone()
+                (kc if what == "k" else vc)[0, row, 2, slot, 37] = float("nan")
+                got = step(kc, vc)
+                assert torch.equal(got[others], ref[others]) and torch.isnan(got[row]).all()
+    finally:
+        F.fleet_destroy(f)
+
+
 @pytest.mark.parametrize("batch,max_batch,form", [(20, 32, WHOLE), (64, 64, END_TO_END)])
 def test_bad_positions_and_pages_under_a_plan(batch, max_batch, form):
     """A position outside the cache, a page outside the pool and a table that is too short end a step that runs by plan as they end any
