@@ -378,6 +378,53 @@ def test_attention_beside_tiles_of_the_whole_batch(nq, nkv, batch, lengths):
 
 
 @pytest.mark.parametrize("paged", [False, True])
+def test_attention_output_beside_tiles_of_the_whole_batch_is_the_quotient(paged):
+    """A row of attention is its sum divided by the sum of weights, rounded once to fp32 and once to bf16: a product with the reciprocal rounds once more.
+    Zero inputs make all scores 0 and all weights 1, and the values add up, exactly and in any order, to n times a midpoint of two bf16 numbers: the
+    quotient is that midpoint, and goes to the even one.  wo is the identity and the FFN adds nothing, so hidden_out is the attention output."""
+    batch, nkv, cap = 100, 8, 1030
+    sh = si.Shape(1, 1024, 8, nkv, 128, 9216, 0, batch, cap)
+    rng = np.random.default_rng(8)
+    n = rng.choice([28, 30, 41, 47, 56, 60, 61, 63], batch)       # keys of a sequence, the new one (of value 0) among them
+    n[::9] = rng.choice([976, 987, 1008, 1013, 1020], len(n[::9]))   # several workers' keys
+    mid = rng.integers(128, 256, (batch, nkv, 128)) * 2 + 1
+    total = n[:, None, None] * mid
+    as_bf16 = lambda a: torch.from_numpy(a.astype(np.float32)).to(torch.bfloat16).float().numpy()
+    want = as_bf16(mid / 4096)
+    of_reciprocal = as_bf16(total.astype(np.float32) * (np.float32(1) / n.astype(np.float32))[:, None, None] / np.float32(4096))
+    for part in (n < 100, n > 100):
+        assert (of_reciprocal[part] != want[part]).mean() > 0.05    # (the test would see it)
+    v = np.zeros((batch, nkv, cap, 128), np.float32)
+    for b in range(batch):
+        left = total[b].astype(np.int64)
+        for slot in rng.permutation(n[b] - 1)[:3]:
+            e = np.maximum(np.floor(np.log2(np.maximum(left, 1))).astype(np.int64) - 7, 0)
+            v[b, :, slot] = left >> e << e                          # the eight leading bits
+            left = left - (left >> e << e)
+        assert (left == 0).all()
+    m = Model(sh, seed=44, batch=batch, positions=(n - 1).astype(np.int32))
+    m.hidden.zero_()
+    m.vc[0, :batch] = torch.from_numpy(v / 4096).to("cuda", torch.bfloat16)
+    m.w["wo"][0].copy_(torch.eye(1024))
+    m.w["wdown"][0].zero_()
+    out = torch.full((batch, sh.hidden), float("nan"), device="cuda", dtype=torch.float32)
+    print(f"quotient, paged {paged}", flush=True)
+    f = F.fleet_create(sh.asdict(), m.w, 0, 0, 0)
+    try:
+        assert F.parse_graph(F.fleet_graph_dump_run(f, batch))["header"]["run_tile_m"] == 128
+        if paged:
+            table = torch.randperm(17 * batch, generator=torch.Generator().manual_seed(2)).to(torch.int32).view(batch, 17)
+            kp, vp = _pools(m.kc, m.vc, batch, 64, table)
+            F.fleet_decode_step_paged(f, batch, m.hidden, None, kp, vp, table.cuda(), 64, 17 * batch, 17, m.pos, out, None)
+        else:
+            F.fleet_decode_step(f, batch, m.hidden, None, m.kc, m.vc, m.pos, out, None)
+        assert F.fleet_last_status(f)["code"] == 0 and F.fleet_last_plan(f) == [END_TO_END] * 8
+    finally:
+        F.fleet_destroy(f)
+    assert (out.cpu().numpy().reshape(batch, nkv, 128) != want).sum() == 0
+
+
+@pytest.mark.parametrize("paged", [False, True])
 def test_infinities_and_nans_beside_tiles_of_the_whole_batch(paged):
     """As test_infinities_and_nans_in_the_cache_stay_with_their_sequence, where a wavefront walks the keys of several sequences: beyond the
     lengths anything may lie; inside one, a row becomes not a number and the others keep their bits."""
