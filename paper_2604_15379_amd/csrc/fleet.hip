@@ -46,7 +46,7 @@ namespace {
 
 using namespace fleetg;
 
-constexpr size_t LDS_BYTES = 128 * 1024;  // > half of a CU's 160 KB: one worker per CU
+using dev::LDS_BYTES;
 constexpr int TRACE_CAP = 2048;           // records per worker
 constexpr int MAX_DEVICES = 64;
 
@@ -446,8 +446,8 @@ int upload_graph(DevGraph* dg, const fleet* f, const void* const* gemm_copies, c
     memcpy(d + dev::FAT_W, &w[tw[T_OP]], sizeof(void*));
     memcpy(d + dev::FAT_W2, &w2[tw[T_OP]], sizeof(void*));
     d[dev::FAT_ID] = t;
-    if (tw[T_WAIT_EVENT] >= 0) d[dev::T_WAIT_NEED] = g.events[(size_t)tw[T_WAIT_EVENT] * EVENT_WORDS + E_THRESHOLD];
-    if (tw[T_SIGNAL_EVENT] >= 0) d[dev::T_SIG_KIND] = g.events[(size_t)tw[T_SIGNAL_EVENT] * EVENT_WORDS + E_KIND];
+    if (tw[T_WAIT_EVENT] >= 0) d[T_WAIT_NEED] = g.events[(size_t)tw[T_WAIT_EVENT] * EVENT_WORDS + E_THRESHOLD];
+    if (tw[T_SIGNAL_EVENT] >= 0) d[T_SIG_KIND] = g.events[(size_t)tw[T_SIGNAL_EVENT] * EVENT_WORDS + E_KIND];
   }
   // CU-tasks dealt inside one XCD: how many of them signal the task's event from that XCD
   for (int x = 0; x < n_xcd; ++x)
@@ -464,8 +464,7 @@ int upload_graph(DevGraph* dg, const fleet* f, const void* const* gemm_copies, c
   // merge, the per-XCD copies of the device counters (rows on their own cache lines), and
   // (MFMA graphs) the arrival counters of split-K GEMM tiles
   if (g.n_events() > dev::ECACHE) return FLEET_EINVAL;   // the kernel keeps one table entry per event in LDS
-  dg->gcnt_base = dev::C_EVENTS + g.n_events() * (1 + n_xcd) + dev::N_PAIR +
-                  dev::COPY_GROUPS * n_xcd * ((g.n_events() + 31) & ~31);
+  dg->gcnt_base = dev::C_EVENTS + dev::at_copy(g.n_events(), n_xcd, dev::COPY_GROUPS * n_xcd);
   dg->ctr_words = dg->gcnt_base + (g.header[H_PATH] == P_MFMA ? dev::GEMM_CNT_WORDS : 0);
   return FLEET_OK;
 }

@@ -93,7 +93,9 @@ constexpr int GEMV_LDS_X_BYTES = 96 * 1024;   // LDS the FMA path may fill with 
 //   INGEST/RMSNORM/SWIGLU/FINAL/ARGMAX : A0 batch row
 // T_HINTS (run_graph): HINT_EARLY: the residual rows a chiplet-task adds to are complete before it waits (its workers have waited for a stage behind
 // them); HINT_INV: the caches may be invalidated before an MFMA GEMM's wait instead of after it
-enum { T_OP = 0, T_SCOPE, T_XCD, T_A0, T_A1, T_A2, T_A3, T_WAIT_EVENT, T_SIGNAL_EVENT, T_STAGE, T_HINTS };
+// T_WAIT_NEED, T_SIG_KIND (in uploaded descriptors only, 0 in a graph): device-level signals the wait event needs, kind of the event that is signalled
+enum { T_OP = 0, T_SCOPE, T_XCD, T_A0, T_A1, T_A2, T_A3, T_WAIT_EVENT, T_SIGNAL_EVENT, T_STAGE, T_HINTS, T_WAIT_NEED, T_SIG_KIND, T_END };
+static_assert(T_END <= TASK_WORDS, "");
 constexpr int HINT_EARLY = 1, HINT_INV = 2;
 // event word indices: threshold counts device-level signals (XCDs for a
 // two-level event, tasks for a direct one); n_tasks counts the signalling tasks
