@@ -326,18 +326,25 @@ def test_pairs_laid_end_to_end_where_an_xcd_has_workers_to_spare(batch, max_batc
     assert np.array_equal(traced[0], got[0])
 
 
-@pytest.mark.parametrize("nq,nkv,batch,lengths", [(8, 8, 100, "mixed"), (16, 8, 128, "short"), (6, 2, 65, "mixed"), (32, 8, 97, "equal"), (8, 8, 128, "few long"), (8, 8, 128, "many long"), (4, 1, 70, "short")])
-def test_attention_beside_tiles_of_the_whole_batch(nq, nkv, batch, lengths):
+# forms: what fleet_last_plan says of each XCD.  0 is the graph's tasks in every set here: where pairs lie end to end in these, some are cut.
+# "short" with one kv head: two splits a pair, the second always empty; "equal long": both have keys.  ("40 to": a value of the new token that the two sides round
+# to neighbours, 2^-7 apart where it is between 1 and 2, shows in all heads of the one kv head, times 1 / keys and wo's up to 9: with two keys 0.11, above the bound.)
+@pytest.mark.parametrize("nq,nkv,batch,lengths,forms", [
+    (8, 8, 100, "mixed", [END_TO_END] * 8), (16, 8, 128, "short", [END_TO_END] * 8), (6, 2, 65, "mixed", [0, 0, END_TO_END, END_TO_END] * 2), (32, 8, 97, "equal", [END_TO_END] * 8),
+    (8, 8, 128, "few long", [END_TO_END] * 8), (8, 8, 128, "many long", [0] * 8), (4, 1, 70, "short", [0] * 8), (4, 1, 70, "40 to 1000", [WHOLE] * 6 + [0, WHOLE]),
+    (3, 1, 128, "40 to 1000", [WHOLE] * 8), (4, 1, 70, "equal long", [0] * 8)])
+def test_attention_beside_tiles_of_the_whole_batch(nq, nkv, batch, lengths, forms):
     """65 to 128 rows of a model that runs tiles of the whole batch: every wavefront walks keys of its own over the ends of pairs.  Lengths at the edges of octs, of
     a wavefront's part and of a worker's piece (empty and single-key caches, pairs inside one wavefront, over several, over several workers, more pairs in
     a piece than a worker has room for), contiguous and paged; equal to the oracle, a traced launch and a second one bit for bit."""
     sh = si.Shape(1, 1024, nq, nkv, 128, 9216, 0, batch, 1100)
     rng = np.random.default_rng(batch + nkv)
-    pos = {"mixed": rng.integers(0, 700, batch), "short": rng.integers(0, 40, batch), "equal": np.full(batch, 333), "few long": rng.integers(0, 9, batch), "many long": rng.integers(0, 9, batch)}[lengths].astype(np.int32)
-    if lengths != "equal":
+    pos = {"mixed": rng.integers(0, 700, batch), "short": rng.integers(0, 40, batch), "equal": np.full(batch, 333), "few long": rng.integers(0, 9, batch), "many long": rng.integers(0, 9, batch), "40 to 1000": np.random.default_rng(5).integers(40, 1001, batch),
+           "equal long": np.full(batch, 900)}[lengths].astype(np.int32)
+    if lengths in ("mixed", "short", "few long", "many long"):
         edges = [0, 1, 7, 8, 9, 31, 32, 33, 63, 64, 65, 255, 256, 257] if lengths == "mixed" else [0, 1, 7, 8, 9, 1, 0]
         pos[5:5 + len(edges)] = edges
-    if lengths.endswith("long"):
+    if lengths in ("few long", "many long"):
         pos[:4 if lengths == "few long" else 12] = 1099 - rng.integers(0, 9)
     m = Model(sh, seed=41 + nkv, batch=batch, positions=pos)
     m.w["wo"][0].mul_(100.0)
@@ -348,7 +355,7 @@ def test_attention_beside_tiles_of_the_whole_batch(nq, nkv, batch, lengths):
     try:
         assert F.parse_graph(F.fleet_graph_dump_run(f, batch))["header"]["run_tile_m"] == 128
         got = m.run_gpu(fleet=f)
-        assert F.fleet_last_plan(f)[0] == {"equal": END_TO_END, "many long": 0}.get(lengths, F.fleet_last_plan(f)[0])
+        assert F.fleet_last_plan(f) == forms
         assert_close(got[0], ho, "hidden_out")
         check_new_kv(m, got[2], got[3], k, v)
         assert np.array_equal(m.run_gpu(fleet=f)[0], got[0])
@@ -358,7 +365,7 @@ def test_attention_beside_tiles_of_the_whole_batch(nq, nkv, batch, lengths):
         hout = torch.full((batch, sh.hidden), float("nan"), device="cuda", dtype=torch.float32)
         print("  paged", flush=True)
         F.fleet_decode_step_paged(f, batch, m.hidden, None, kc, vc, table.cuda(), 64, per * batch, per, m.pos, hout, None)
-        assert F.fleet_last_status(f)["code"] == 0
+        assert F.fleet_last_status(f)["code"] == 0 and F.fleet_last_plan(f) == forms
         assert_close(hout.cpu().numpy(), ho, "hidden_out, paged")
         for row, kind in ((0, "position"), (batch // 2, "position"), (5, "page"), (batch - 1, "page")):   # reported, and the next step is right
             bad_pos, bad_table = m.pos.clone(), table.clone()
@@ -375,6 +382,39 @@ def test_attention_beside_tiles_of_the_whole_batch(nq, nkv, batch, lengths):
         F.fleet_destroy(f)
     traced = m.run_gpu(0, 0, F.FLAG_TRACE)
     assert np.array_equal(traced[0], got[0])
+
+
+@pytest.mark.parametrize("lengths,form", [("mixed", END_TO_END), ("equal", 0)])   # pairs cut; three whole pairs a worker
+@pytest.mark.parametrize("page", [64, 128, 256])
+def test_page_sizes_beside_tiles_of_the_whole_batch(page, lengths, form):
+    """Two layers of 96 sequences over a paged cache whose pages hold several steps of a wavefront's walk, lengths at the edges of pages: the bits of the
+    contiguous cache, the new tokens' keys and values in their slots, nothing else touched."""
+    batch, cap = 96, 700
+    sh = si.Shape(2, 1024, 8, 8, 128, 9216, 0, batch, cap)
+    pos = np.full(batch, 300, np.int32) if lengths == "equal" else np.random.default_rng(page).integers(0, cap, batch).astype(np.int32)
+    if lengths == "mixed":
+        pos[3:3 + 13] = [0, 1, 63, 64, 65, 127, 128, 129, 255, 256, 257, 512, cap - 1]
+    m = Model(sh, seed=45, batch=batch, positions=pos)
+    (ho, _), _, _ = m.run_oracle()
+    per = -(-cap // page)
+    table = torch.randperm(per * batch, generator=torch.Generator().manual_seed(page)).to(torch.int32).view(batch, per)
+    kp, vp = _pools(m.kc, m.vc, batch, page, table)
+    hout = torch.full((batch, sh.hidden), float("nan"), device="cuda", dtype=torch.float32)
+    f = F.fleet_create(sh.asdict(), m.w, 0, 0, 0)
+    try:
+        assert F.parse_graph(F.fleet_graph_dump_run(f, batch))["header"]["run_tile_m"] == 128
+        print(f"page {page}, {lengths}", flush=True)
+        ref = m.run_gpu(fleet=f)
+        assert F.fleet_last_plan(f) == [form] * 8
+        F.fleet_decode_step_paged(f, batch, m.hidden, None, kp, vp, table.cuda(), page, per * batch, per, m.pos, hout, None)
+        assert F.fleet_last_status(f)["code"] == 0 and F.fleet_last_plan(f) == [form] * 8
+    finally:
+        F.fleet_destroy(f)
+    assert_close(ref[0], ho, "hidden_out")
+    assert np.array_equal(hout.cpu().numpy(), ref[0])
+    k, v = (torch.from_numpy(c.view(np.int16)).cuda().view(torch.bfloat16) for c in ref[2:4])
+    for got, want in zip((kp, vp), _pools(k, v, batch, page, table)):
+        assert torch.equal(got.view(torch.int16), want.view(torch.int16))
 
 
 @pytest.mark.parametrize("paged", [False, True])
