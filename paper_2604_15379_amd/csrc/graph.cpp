@@ -363,9 +363,8 @@ Graph build_decode_graph(const fleet_shape_t& s, int batch, int n_xcd, int n_wor
   const bool fuse_norm_mfma = path == P_MFMA && !(s.flags & FLEET_FLAG_SEPARATE_NORM) &&
                               mfma_blocks(tm) <= FUSED_NORM_MAX_BLOCKS && H % 64 == 0 && H <= 32768;
   auto xmode = [&](int K) { return path == P_FMA && (int64_t)batch * K * 2 <= GEMV_LDS_X_BYTES ? X_LDS_COPY : X_GLOBAL; };
-  // weight blocks requested before the wait (bits 10..11 of aux2; the kernel requests three).  Measured at batch 1:
-  // requesting only one block after the short O-projection stage (to reach the poll
-  // sooner) is slower than requesting the full depth everywhere.
+  // Bits 10..11 of aux2: weight blocks requested before the wait.  A constant part of the graph's words; gemv_task requests three and does not look.
+  // (Only one block after the short O-projection stage, to reach the poll sooner, is slower at batch 1 than the full depth everywhere.)
   const int PRE2 = 3 << 10;
 
   // FMA path: the workers that run an XCD's attention tasks (its first ranks: the tasks are

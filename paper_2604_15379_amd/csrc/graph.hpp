@@ -74,8 +74,8 @@ enum {
 // O_AUX2 of a GEMM op: low byte = WKind of the op's second pointer (W_NONE if none): the gain
 // of the fused RMSNorm (activation mode X_LDS_NORM), else the weights of the next GEMM, whose
 // first block the op's idle workers pull into the L2 (O_AUX then holds that matrix's gate rows),
-// bits 8..9 = activation mode of the FMA path (XMode), bits 10..11 = weight blocks the FMA
-// path requests before its dependency wait (always 3); MFMA path: bits 12..15 = units per tile,
+// bits 8..9 = activation mode of the FMA path (XMode), bits 10..11 = 3, the weight blocks the FMA
+// path requests before its dependency wait (read by no kernel); MFMA path: bits 12..15 = units per tile,
 // bits 16..19 = k-slices of the split-K plan (1 = no split), bit 20 = counter set of the
 // split-K arrival counters (isolated GEMM repetitions alternate), bit 21 = register-resident
 // weights (MfmaPlan::resident), bit 22 = the op reads the fp32 residual stream and normalises
