@@ -21,7 +21,7 @@ _DEPS = [os.path.join(_CSRC, n) for n in ("fleet.hip", "graph.cpp", "kernel_vari
         [os.path.join(_PKG, "..", "include", "fleet.h")]
 
 _FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
-          # packed-FP32 instructions are not to be generated on the test machines
+          # packed-FP32 instructions are not to be generated: some forms give wrong results on this hardware
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
           "-Wno-unused-value"]
 
