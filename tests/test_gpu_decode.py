@@ -1175,7 +1175,7 @@ def test_whole_batch_tiles_in_a_step(batch):
     assert_close(low[0], got[0], "64-row tiles")
 
 
-@pytest.mark.parametrize("batch,kv", [(96, 64), (100, 900)])   # attention by the graph's tasks, and by a plan
+@pytest.mark.parametrize("batch,kv", [(96, 64), (100, 900)])   # attention in whole pairs, and by a plan that cuts some
 def test_whole_batch_tiles_from_every_entry_point(batch, kv):
     """The step over a paged cache, layer by layer on an fp32 residual stream and as the first of several greedy steps has
     the bits of the step over a contiguous cache; three greedy steps in one launch those of three launches."""
